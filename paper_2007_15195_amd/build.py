@@ -25,6 +25,8 @@ SOURCES = [
     "kernels_plan.hip",
     "kernels_setup.hip",
     "kernels_qmc.hip",
+    "kernels_qmc_f64.hip",
+    "kernels_qmc_f64_long.hip",
     "kernels_finalize.hip",
     "runtime.cpp",
     "server.cpp",

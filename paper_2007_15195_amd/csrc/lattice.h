@@ -32,13 +32,20 @@ __device__ __forceinline__ uint64_t lattice_shift(uint64_t seed, int64_t term, i
   return splitmix64(seed, salt | (1ULL << 62) | ((uint64_t)term << 22) | ((uint64_t)r << 6) | (uint64_t)dim);
 }
 
-// FP64 coordinate (2 floor(W / 2^12) + 1) 2^-53.
+// FP64 coordinate (2 floor(W / 2^12) + 1) 2^-53, W = |2U - 2^64| (2^64 saturates).
+// With V = U for U >= 2^63 and V = U - 1 below (so that U = 0 joins the upper
+// half, where it saturates) and f = floor((V mod 2^63) / 2^11) 2^-52, placed in
+// the mantissa of 1 + f, the coordinate is t = f + 2^-53 in the upper half and
+// 1 - t in the lower; every operation is exact.
 __device__ __forceinline__ double lattice_coord_f64(uint64_t U) {
-  const uint64_t twice = U << 1;
-  uint64_t W = (U >> 63) ? twice : (0 - twice);
-  W = U ? W : ~0ULL;
-  const uint64_t odd = (W >> 11) | 1ULL;   // 2 floor(W/2^12) + 1 < 2^53
-  return (double)odd * 0x1p-53;
+  const int32_t lower = (int32_t)~(uint32_t)(U >> 32) >> 31;   // -1 for U < 2^63, else 0
+  const uint64_t V = U + (uint64_t)(int64_t)lower;
+  const uint32_t vh = (uint32_t)(V >> 32);
+  const uint32_t mh = ((vh >> 11) & 0xfffffu) | 0x3ff00000u;
+  const uint32_t ml = __builtin_amdgcn_alignbit(vh, (uint32_t)V, 11);
+  const double t = __longlong_as_double((long long)(((uint64_t)mh << 32) | ml)) - (1.0 - 0x1p-53);
+  const uint32_t one = ~(uint32_t)((int32_t)vh >> 31) & 0x3ff00000u;   // the high word of 1.0 in the lower half
+  return fabs(t - __longlong_as_double((long long)((uint64_t)one << 32)));
 }
 
 // FP32 coordinate of U, from its upper 32 bits only: with s = U_hi - 2^31 as a

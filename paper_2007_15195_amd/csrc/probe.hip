@@ -8,6 +8,7 @@
 
 #include "device_math_f32.h"
 #include "device_math_f64.h"
+#include "device_nodes_f64.h"
 #include "lattice.h"
 #include "runtime.h"
 #include "vecchia.h"
@@ -44,9 +45,11 @@ __global__ __launch_bounds__(kProbeThreads) void probe_math(int what, int64_t n,
     // the split path's quantile from log2 q = x directly (its exponents reach -2^20)
     o0 = ninv_tail_from_log2_split((float)x);
   } else if (what == VECCHIA_PROBE_PHI_F64) {
-    o0 = phi64(x);
+    // as the FP64 loop: the node table, the fitted ratio below it
+    o0 = x >= -kPhiNodeMax ? phi_nodes(kNormNodeTable, fmin(x, kPhiNodeMax)) : phi64(x);
   } else {
-    o0 = ninv64(x);
+    const double q = fmin(x, 1.0 - x);
+    o0 = q >= kNinvNodeMin ? copysign(ninv_nodes(kNormNodeTable, q), x - 0.5) : ninv64(x);
   }
   out[3 * i] = o0;
   out[3 * i + 1] = o1;

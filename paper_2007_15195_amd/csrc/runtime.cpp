@@ -311,6 +311,7 @@ vecchia_status Batch::create(const std::vector<vecchia_plan_s*>& plans,
       int64_t e = i + 1;
       while (e < NT && sk[e] == k) ++e;
       if (k >= 1) {
+        if (prec == VECCHIA_FP32_LOOP) b->f32_max_k_ = std::max(b->f32_max_k_, k);
         RangeDesc r;
         r.item_begin = e - i;   // term count; turned into the item prefix below
         r.term_begin = i;
@@ -318,7 +319,8 @@ vecchia_status Batch::create(const std::vector<vecchia_plan_s*>& plans,
         r.K = k;
         r.items_per_term = passes * R * C;
         r.n_chunks = C;
-        by_k[{k, prec, P->block > 0}].push_back(r);
+        // the FP64 kernels take plain and joint terms alike
+        by_k[{k, prec, prec == VECCHIA_FP32_LOOP && P->block > 0}].push_back(r);
       }
       i = e;
     }
@@ -503,8 +505,8 @@ vecchia_status Batch::enqueue(hipStream_t s, bool allow_profile) {
   // grid that finds nothing to do when no term was promoted)
   const bool redo = any_f32_ && ipt_max_ > 0;
   if (e == hipSuccess && redo)
-    e = launch_qmc_promoted(d_desc_, n, d_term_bases_, d_aux64_, d_Z_, d_sums_, d_plist_, d_pctr_, plist_cap_,
-                            ipt_max_, s);
+    e = launch_qmc_promoted(f32_max_k_, d_desc_, n, d_term_bases_, d_aux64_, d_Z_, d_sums_, d_plist_, d_pctr_,
+                            plist_cap_, ipt_max_, s);
   if (e == hipSuccess)
     e = launch_finalize_terms(d_desc_, n, d_term_bases_, total_terms_, d_aux64_, d_sums_, d_term_res_, redo, s);
   // then the terms whose FP32 estimate the finalize found heavy-tailed: FP64
@@ -514,8 +516,8 @@ vecchia_status Batch::enqueue(hipStream_t s, bool allow_profile) {
     e = launch_setup_redo(d_desc_, n, d_term_bases_, max_vars_, d_aux64_, d_aux32_, d_plist_ + plist_cap_, d_pctr_ + 2,
                           plist_cap_, s);
   if (e == hipSuccess && redo)
-    e = launch_qmc_promoted(d_desc_, n, d_term_bases_, d_aux64_, d_Z_, d_sums_, d_plist_ + plist_cap_, d_pctr_ + 2,
-                            plist_cap_, ipt_max_, s);
+    e = launch_qmc_promoted(f32_max_k_, d_desc_, n, d_term_bases_, d_aux64_, d_Z_, d_sums_, d_plist_ + plist_cap_,
+                            d_pctr_ + 2, plist_cap_, ipt_max_, s);
   if (e == hipSuccess && redo)
     e = launch_finalize_redo(d_desc_, n, d_term_bases_, d_aux64_, d_sums_, d_term_res_, d_plist_ + plist_cap_,
                              d_pctr_ + 2, plist_cap_, s);

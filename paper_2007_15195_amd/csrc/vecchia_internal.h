@@ -141,9 +141,23 @@ hipError_t launch_qmc(int K, int precision, bool block, const InstDesc* d_insts,
 // The handed-over terms of FP32 instances in FP64: a persistent grid takes
 // (term, item) pairs from a device-side list (ctr[0] entries, at most cap;
 // ipt_max items per term at most; ctr[1] is the work counter) until none is left.
-hipError_t launch_qmc_promoted(const InstDesc* d_insts, int n_inst, const int64_t* d_term_bases, const Aux64* aux64,
-                               const uint64_t* d_Z, double* sums, const int32_t* list, int64_t* ctr,
-                               int64_t cap, int ipt_max, hipStream_t s);
+// K: the most SOV steps of any term of the FP32 instances.
+hipError_t launch_qmc_promoted(int K, const InstDesc* d_insts, int n_inst, const int64_t* d_term_bases,
+                               const Aux64* aux64, const uint64_t* d_Z, double* sums, const int32_t* list,
+                               int64_t* ctr, int64_t cap, int ipt_max, hipStream_t s);
+// FP64 kernels are built for kc = 2, 4, ..., 62, 63 steps; a chain of K steps runs in the next size up.
+constexpr int kF64ShortK = 32;
+constexpr int f64_kernel_size(int K) { return K >= kMaxM ? kMaxM : (K + 1) / 2 * 2; }
+hipError_t launch_qmc_f64_short(int kc, const InstDesc* insts, const RangeDesc* ranges, int n_ranges, int64_t n_items,
+                                const Aux64* aux64, const uint64_t* Z, double* sums, hipStream_t s);
+hipError_t launch_qmc_f64_long(int kc, const InstDesc* insts, const RangeDesc* ranges, int n_ranges, int64_t n_items,
+                               const Aux64* aux64, const uint64_t* Z, double* sums, hipStream_t s);
+hipError_t launch_qmc_promoted_short(int kc, const InstDesc* insts, int n_inst, const int64_t* term_bases,
+                                     const Aux64* aux64, const uint64_t* Z, double* sums, const int32_t* list,
+                                     int64_t* ctr, int64_t cap, int ipt_max, hipStream_t s);
+hipError_t launch_qmc_promoted_long(int kc, const InstDesc* insts, int n_inst, const int64_t* term_bases,
+                                    const Aux64* aux64, const uint64_t* Z, double* sums, const int32_t* list,
+                                    int64_t* ctr, int64_t cap, int ipt_max, hipStream_t s);
 // Scale-mixture quadrature weights (log), passed by value to the combine kernel.
 constexpr int kMaxMixNodes = 64;
 constexpr int kMixSearch = VECCHIA_MIX_SEARCH_NODES;
