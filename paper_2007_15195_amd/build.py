@@ -25,6 +25,9 @@ SOURCES = [
     "kernels_plan.hip",
     "kernels_setup.hip",
     "kernels_qmc.hip",
+    "kernels_qmc_f32.hip",
+    "kernels_qmc_f32_long.hip",
+    "kernels_qmc_f32_block.hip",
     "kernels_qmc_f64.hip",
     "kernels_qmc_f64_long.hip",
     "kernels_finalize.hip",

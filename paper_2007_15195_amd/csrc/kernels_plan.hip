@@ -18,6 +18,9 @@
 namespace vecchia {
 namespace {
 
+// Neighbour lists of up to this length are sized exactly.
+constexpr int kKnnExactM = 31;
+
 constexpr int kKnnWaves = 8;
 constexpr int kKnnTile = 512;
 
@@ -326,8 +329,8 @@ hipError_t launch_knn(const double* xs, const double* ys, int64_t D, int m, int3
     const hipError_t e = build_grid(xs, ys, D, *grid, s);
     if (e != hipSuccess) return e;
   }
-  if (m <= kMaxUnrolledK)
-    return knn_switch(m, xs, ys, D, nbr, kcnt, grid, group, s, std::make_integer_sequence<int, kMaxUnrolledK>{});
+  if (m <= kKnnExactM)
+    return knn_switch(m, xs, ys, D, nbr, kcnt, grid, group, s, std::make_integer_sequence<int, kKnnExactM>{});
   // larger sets: lists of capacity 40, 48, 56 or 64 holding the m wanted
   if (m <= 40) return knn_dispatch<40>(xs, ys, D, nbr, kcnt, grid, group, m, s);
   if (m <= 48) return knn_dispatch<48>(xs, ys, D, nbr, kcnt, grid, group, m, s);

@@ -10,6 +10,7 @@
 #include "device_math_f64.h"
 #include "device_nodes_f64.h"
 #include "lattice.h"
+#include "normal_tables_f32.h"
 #include "runtime.h"
 #include "vecchia.h"
 
@@ -37,9 +38,15 @@ __global__ __launch_bounds__(kProbeThreads) void probe_math(int what, int64_t n,
     o2 = fl;
   } else if (what == VECCHIA_PROBE_NINV_F32) {
     // the SOV loop's quantile of q = x (0 < q <= 1/2, rounded to FP32):
-    // z = -Phi^{-1}(q) from log2 q
+    // z = -Phi^{-1}(q) from its cell, below the cells from log2 q
     const float q = (float)x;
-    o0 = ninv_tail_from_log2(fast_log2(q));
+    if (q >= 0x1p-15f) {
+      const float* c = kQuantTable[((__builtin_bit_cast(uint32_t, q) >> 14) & 0x1ff0u) / 16];
+      const float d = q - c[3];
+      o0 = fmaf(fmaf(c[2], d, c[1]), d, c[0]);
+    } else {
+      o0 = ninv_tail_from_log2_split(fast_log2(q));
+    }
     o1 = q;
   } else if (what == VECCHIA_PROBE_NINV_LOG2_F32) {
     // the split path's quantile from log2 q = x directly (its exponents reach -2^20)
@@ -48,8 +55,9 @@ __global__ __launch_bounds__(kProbeThreads) void probe_math(int what, int64_t n,
     // as the FP64 loop: the node table, the fitted ratio below it
     o0 = x >= -kPhiNodeMax ? phi_nodes(kNormNodeTable, fmin(x, kPhiNodeMax)) : phi64(x);
   } else {
+    // (the loop's value at exactly 1/2 is 1.2e-18, the fitted ratio's is 0)
     const double q = fmin(x, 1.0 - x);
-    o0 = q >= kNinvNodeMin ? copysign(ninv_nodes(kNormNodeTable, q), x - 0.5) : ninv64(x);
+    o0 = q >= kNinvNodeMin && q < 0.5 ? copysign(ninv_nodes(kNormNodeTable, q), x - 0.5) : ninv64(x);
   }
   out[3 * i] = o0;
   out[3 * i + 1] = o1;

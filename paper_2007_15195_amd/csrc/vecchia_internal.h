@@ -12,9 +12,6 @@ constexpr int kMaxM = VECCHIA_MAX_M;   // conditioning-set size limit
 constexpr int kMaxVars = kMaxM + 1;    // variables per term
 constexpr double kPromoteZ = -4.0;     // FP32 instances: terms with a limit below this many SDs run in FP64
 constexpr double kRedoSe = 0.02;       // FP32 instances: terms whose log-term SE exceeds this run again in FP64
-// Chains of up to this many steps run fully unrolled with y in registers;
-// longer ones (up to kMaxM) run in the general kernel with y in LDS.
-constexpr int kMaxUnrolledK = 31;
 constexpr int kFinalizeThreads = 256;
 // A launch may hold fewer than 2^32 work-items in total; per-term and per-item
 // kernels are split into launches of at most this many threads.
@@ -145,9 +142,17 @@ hipError_t launch_qmc(int K, int precision, bool block, const InstDesc* d_insts,
 hipError_t launch_qmc_promoted(int K, const InstDesc* d_insts, int n_inst, const int64_t* d_term_bases,
                                const Aux64* aux64, const uint64_t* d_Z, double* sums, const int32_t* list,
                                int64_t* ctr, int64_t cap, int ipt_max, hipStream_t s);
-// FP64 kernels are built for kc = 2, 4, ..., 62, 63 steps; a chain of K steps runs in the next size up.
-constexpr int kF64ShortK = 32;
-constexpr int f64_kernel_size(int K) { return K >= kMaxM ? kMaxM : (K + 1) / 2 * 2; }
+// The QMC kernels are built for kc = 2, 4, ..., 62, 63 steps (joint FP32 terms:
+// 4, 8, ..., 60, 63); a chain of K steps runs in the next size up.
+constexpr int kQmcShortK = 32;
+constexpr int qmc_kernel_size(int K) { return K >= kMaxM ? kMaxM : (K + 1) / 2 * 2; }
+constexpr int f32_block_kernel_size(int K) { return K > 60 ? kMaxM : (K + 3) / 4 * 4; }
+hipError_t launch_qmc_f32_short(int kc, const InstDesc* insts, const RangeDesc* ranges, int n_ranges, int64_t n_items,
+                                const Aux32* aux32, const uint64_t* Z, double* sums, hipStream_t s);
+hipError_t launch_qmc_f32_long(int kc, const InstDesc* insts, const RangeDesc* ranges, int n_ranges, int64_t n_items,
+                               const Aux32* aux32, const uint64_t* Z, double* sums, hipStream_t s);
+hipError_t launch_qmc_f32_block(int kc, const InstDesc* insts, const RangeDesc* ranges, int n_ranges, int64_t n_items,
+                                const Aux32* aux32, const uint64_t* Z, double* sums, hipStream_t s);
 hipError_t launch_qmc_f64_short(int kc, const InstDesc* insts, const RangeDesc* ranges, int n_ranges, int64_t n_items,
                                 const Aux64* aux64, const uint64_t* Z, double* sums, hipStream_t s);
 hipError_t launch_qmc_f64_long(int kc, const InstDesc* insts, const RangeDesc* ranges, int n_ranges, int64_t n_items,
