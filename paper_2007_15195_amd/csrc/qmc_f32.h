@@ -30,7 +30,9 @@
 //  * has one rare-case test: a quantile argument below 2^-15, which every
 //    factor below 2^-15 implies in the next step. Such lanes take the
 //    previous factor and the quantile again in the accurate split form below.
-// FIGURES
+// Measured over whole launches (8192 x 8 points, thresholds at 1.28), CU-clocks a
+// step now and with one-wave workgroups, fitted ratios and rows in LDS:
+// k = 10: 27.9 (38.8); k = 20: 33.1 (43.1); k = 31: 39.7 (56.7).
 //
 // Rare lanes (cold32, cold32_first): factors are e = em * 2^en, with en = 0
 // except for lower-tail factors below 2^-60 (t < -9.1), which keep
@@ -43,9 +45,11 @@
 //
 // K is the most steps a kernel runs, a template parameter, so that the chain is
 // unrolled and y[] stays in registers; a term with k < K leaves the chain after
-// step k (a scalar compare per step). The term's scaled rows are staged in LDS
-// once per work item and read as broadcasts. A workgroup is four waves with
-// their own items around one table (8 KB), eight workgroups to a compute unit.
+// step k (a scalar compare per step). The term's scaled rows come through scalar
+// loads as scalar operands: 1.05 clocks a coefficient, where LDS broadcasts took
+// 0.6 on the vector unit and 1.2 on the LDS pipe beside the table's gathers, 2.1
+// measured. A workgroup is four waves with their own items around one table
+// (8 KB), eight workgroups to a compute unit.
 #pragma once
 #include "vecchia_internal.h"
 
@@ -68,6 +72,7 @@ constexpr int kF32AdvanceK = 24;
 constexpr int f32_min_waves(int K) { return K <= 12 ? 8 : K <= 18 ? 6 : K <= 24 ? 5 : K <= 32 ? 6 : K <= 48 ? 5 : 4; }
 
 using ScalarGen32 = const __attribute__((address_space(4))) uint64_t*;
+using ScalarRows32 = const __attribute__((address_space(4))) float*;
 
 // p * a + literal and a * literal + c, the coefficients in the instruction.
 #define VECCHIA_FMAAK(p, a, k)                                                                                      \
@@ -91,6 +96,26 @@ __device__ __forceinline__ float tail_f32(float v) {
   VECCHIA_FMAAK(p, a, kTailPoly[1]);
   VECCHIA_FMAAK(p, a, kTailPoly[0]);
   return fast_exp2(p);
+}
+
+// phi_f32 with the ratio's coefficients in the instructions.
+__device__ __forceinline__ PhiParts phi_f32_lit(float v) {
+  const float a = fabsf(v);
+  PhiParts o;
+  o.f = -(v * v);
+  float p = kRP[3], q = kRQ[4];
+  VECCHIA_FMAAK(p, a, kRP[2]);
+  VECCHIA_FMAAK(p, a, kRP[1]);
+  VECCHIA_FMAAK(p, a, kRP[0]);
+  VECCHIA_FMAAK(q, a, kRQ[3]);
+  VECCHIA_FMAAK(q, a, kRQ[2]);
+  VECCHIA_FMAAK(q, a, kRQ[1]);
+  VECCHIA_FMAAK(q, a, kRQ[0]);
+  o.R = p * fast_rcp(q);
+  o.m = fast_exp2(o.f) * o.R;
+  o.neg = v <= 0.0f;
+  o.em = o.neg ? o.m : 1.0f - o.m;
+  return o;
 }
 
 // -Phi^{-1}(q) from the cells; any q outside their range addresses some slot.
@@ -146,15 +171,15 @@ struct Chain32 {
 
 // Step A and, through the recursion, the steps after it; returns with v_k.
 template <int A, int K, bool BLOCK>
-__device__ __forceinline__ void steps_f32(Chain32<K>& s, uint64_t* U, const uint64_t* sh, ScalarGen32 Z, const float* srow,
+__device__ __forceinline__ void steps_f32(Chain32<K>& s, uint64_t* U, const uint64_t* sh, ScalarGen32 Z, ScalarRows32 rows,
                                           const float4* cells, float c24, const Aux32& ax, bool split0, int k, int sp,
-                                          uint64_t pt) {
+                                          uint32_t pt) {
   uint32_t hi;
   if constexpr (K <= kF32AdvanceK) {
     hi = (uint32_t)(U[A - 1] >> 32);
     U[A - 1] += Z[A - 1] << 6;
   } else {
-    hi = (uint32_t)((pt * Z[A - 1] + sh[A - 1]) >> 32);
+    hi = (uint32_t)(((uint64_t)pt * Z[A - 1] + sh[A - 1]) >> 32);
   }
   // lattice_coord_f32: 1 - w = |g + 1/2| 2^-23, exact
   const float g = (float)((int32_t)hi >> 8);
@@ -195,15 +220,15 @@ __device__ __forceinline__ void steps_f32(Chain32<K>& s, uint64_t* U, const uint
     s.de = s.qe;
   }
   constexpr int ro = A * (A + 1) / 2;
-  float v = srow[ro + A];
+  float v = rows[ro + A];
 #pragma unroll
-  for (int c = 0; c < A; ++c) v = fmaf(-srow[ro + c], s.y[c], v);
+  for (int c = 0; c < A; ++c) v = fmaf(-rows[ro + c], s.y[c], v);
   s.v = v;
   if constexpr (A < K) {
     if (A == k) return;
     if (BLOCK && A >= sp) {
       // a factor of the numerator's tail: its complement to full relative accuracy
-      const PhiParts ph = phi_f32(v);
+      const PhiParts ph = phi_f32_lit(v);
       s.em = ph.em;
       s.m = ph.m;
       s.cc = fmaf(ph.neg ? 1.0f - ph.em : ph.m, 1.0f - s.cc, s.cc);
@@ -211,13 +236,13 @@ __device__ __forceinline__ void steps_f32(Chain32<K>& s, uint64_t* U, const uint
       s.m = tail_f32(v);
       s.em = v <= 0.0f ? s.m : 1.0f - s.m;
     }
-    steps_f32<A + 1, K, BLOCK>(s, U, sh, Z, srow, cells, c24, ax, split0, k, sp, pt);
+    steps_f32<A + 1, K, BLOCK>(s, U, sh, Z, rows, cells, c24, ax, split0, k, sp, pt);
   }
 }
 
 template <int K, bool BLOCK>
 __device__ __forceinline__ void item_f32(const Item& it, const Aux32* __restrict__ aux32, const uint64_t* __restrict__ Zg,
-                                         double* __restrict__ sums, float* srow, uint64_t* sh, const float4* cells) {
+                                         double* __restrict__ sums, uint64_t* sh, const float4* cells) {
   const InstDesc& I = *it.I;
   if (uniform(I.promote[it.t]) != 0) return;   // this term runs in FP64 (qmc_promoted)
   const int lane = threadIdx.x & 63;
@@ -240,8 +265,7 @@ __device__ __forceinline__ void item_f32(const Item& it, const Aux32* __restrict
   } else {
     for (int j = lane; j < k; j += 64) sh[j] = lattice_shift(I.seed, it.i, it.sr, j, it.second);
   }
-  const int rows = (k + 1) * (k + 2) / 2;   // rows 0..k of the term's block
-  for (int e = lane; e < rows; e += 64) srow[e] = prep[e];
+  uintptr_t rows_u = (uintptr_t)prep;
   __builtin_amdgcn_wave_barrier();          // the wave's own LDS slice: program order suffices
   float c24 = 0x1p-24f;
   __asm__ volatile("" : "+v"(c24));
@@ -250,7 +274,7 @@ __device__ __forceinline__ void item_f32(const Item& it, const Aux32* __restrict
     // compiler-only barrier: the rows are re-read from LDS in every iteration
     // instead of being held in registers across the loop; the scalars are opaque
     // so that a step compares and loads in place
-    __asm__ volatile("" : "+s"(Z_u), "+s"(k), "+s"(sp)::"memory");
+    __asm__ volatile("" : "+s"(Z_u), "+s"(rows_u), "+s"(k), "+s"(sp)::"memory");
     Chain32<K> s;
     s.em = ax.em0;
     s.m = ax.ec0;
@@ -265,34 +289,30 @@ __device__ __forceinline__ void item_f32(const Item& it, const Aux32* __restrict
       s.qm = __builtin_amdgcn_frexp_mantf(ax.em0);
       if (sp == 0) s.cc = ax.ec0;
     }
-    steps_f32<1, K, BLOCK>(s, U, sh, (ScalarGen32)Z_u, srow, cells, c24, ax, split0, k, sp, (uint64_t)(p0 + lane));
-    // the last factor, to full accuracy
-    const PhiParts ph = phi_f32(s.v);
-    float em = ph.em, en = 0.0f;
-    if (__builtin_expect(any_lane(s.v < -kDeepV), 0)) {
+    steps_f32<1, K, BLOCK>(s, U, sh, (ScalarGen32)Z_u, (ScalarRows32)rows_u, cells, c24, ax, split0, k, sp, (uint32_t)(p0 + lane));
+    // the last factor, to full accuracy; its exponent and the product's are 0
+    // but for rare lanes
+    const PhiParts ph = phi_f32_lit(s.v);
+    double em = (double)ph.em, ec = (double)(ph.neg ? 1.0f - ph.em : ph.m);
+    double den = (double)(BLOCK ? s.dm : s.qm), num = (double)s.qm;
+    if (__builtin_expect(any_lane(s.v < -kDeepV || s.qe != 0 || (BLOCK && s.de != 0)), 0)) {
       if (s.v < -kDeepV) {
         const float f = fmaxf(ph.f, -1048576.0f), fl = floorf(f);
-        em = fast_exp2(f - fl) * ph.R;
-        en = fl;
+        em = ldexp((double)(fast_exp2(f - fl) * ph.R), (int)fl);
+        ec = 1.0 - em;
       }
+      den = ldexp(den, BLOCK ? s.de : s.qe);
+      num = ldexp(num, s.qe);
     }
-    const int enk = (int)en;
-    const float ec = ph.neg ? 1.0f - ldexpf(em, enk) : ph.m;
-    // lanes past the chunk's last point contribute zero
-    const bool in_chunk = p0 + lane <= p_last;
+    if (p0 + 63 > p_last && p0 + lane > p_last) den = num = 0.0;   // past the chunk's last point
+    acc_den += den;
     if (BLOCK) {
-      s.cc = fmaf(ec, 1.0f - s.cc, s.cc);
-      const double den = ldexp((double)(in_chunk ? s.dm : 0.0f), s.de);
-      acc_den += den;
-      acc_num += ldexp((double)(in_chunk ? s.qm : 0.0f) * (double)em, s.qe + enk);
-      acc_cnum = fma(den, (double)s.cc, acc_cnum);
+      ec = (double)fmaf((float)ec, 1.0f - s.cc, s.cc);
+      acc_num = fma(num, em, acc_num);
     } else {
-      const double den = ldexp((double)(in_chunk ? s.qm : 0.0f), s.qe);
-      const double num = ldexp(den * (double)em, enk);
-      acc_den += den;
-      acc_num += num;
-      acc_cnum = fma(den, (double)ec, acc_cnum);
+      acc_num = fma(den, em, acc_num);
     }
+    acc_cnum = fma(den, ec, acc_cnum);
   }
   acc_num = wave_sum(acc_num);
   acc_den = wave_sum(acc_den);
@@ -312,9 +332,7 @@ __global__ __launch_bounds__(64 * kF32Waves) __attribute__((amdgpu_waves_per_eu(
     const InstDesc* __restrict__ insts, const RangeDesc* __restrict__ ranges, int n_ranges,
     const Aux32* __restrict__ aux32, const uint64_t* __restrict__ Zg, double* __restrict__ sums, int64_t item_base,
     int64_t n_items, int items_per_wave) {
-  constexpr int kRowElems = (K + 1) * (K + 2) / 2;
   __shared__ float4 cells[kQuantSlots];
-  __shared__ float srow[kF32Waves][kRowElems];
   __shared__ uint64_t sh[kF32Waves][K > kF32AdvanceK ? K : 1];
   for (int e = threadIdx.x; e < kQuantSlots; e += 64 * kF32Waves)
     cells[e] = reinterpret_cast<const float4*>(kQuantTable)[e < kQuantCells ? e : kQuantCells - 1];
@@ -323,7 +341,7 @@ __global__ __launch_bounds__(64 * kF32Waves) __attribute__((amdgpu_waves_per_eu(
   int64_t g = item_base + block_item(0) * (int64_t)(kF32Waves * items_per_wave) + wv;
   for (int j = 0; j < items_per_wave && g < n_items; ++j, g += kF32Waves) {
     const Item it = decode_item(insts, ranges, n_ranges, g);
-    item_f32<K, BLOCK>(it, aux32, Zg, sums, srow[wv], sh[wv], cells);
+    item_f32<K, BLOCK>(it, aux32, Zg, sums, sh[wv], cells);
   }
 }
 

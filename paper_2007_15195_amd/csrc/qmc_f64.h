@@ -72,7 +72,7 @@ struct Chain64 {
 // Step A and, through the recursion, the steps after it up to min(k, K).
 template <int A, int K>
 __device__ __forceinline__ void steps_f64(Chain64<K>& s, uint64_t* U, const uint64_t* sh, ScalarGen Z, ScalarRows rows,
-                                          const double* nodes, int k, int sp, uint64_t pt) {
+                                          const double* nodes, int k, int sp, uint32_t pt) {
   if (A > k) return;
   if (A == sp) {
     __asm__ volatile("");   // a scalar branch, not a select in every step
@@ -83,7 +83,7 @@ __device__ __forceinline__ void steps_f64(Chain64<K>& s, uint64_t* U, const uint
     Ua = U[A - 1];
     U[A - 1] += Z[A - 1] << 6;
   } else {
-    Ua = pt * Z[A - 1] + sh[A - 1];
+    Ua = (uint64_t)pt * Z[A - 1] + sh[A - 1];
   }
   const double w = lattice_coord_f64(Ua);
   // y = Phi^{-1}(u) from q = min(u, 1 - u) (1 - u is exact for u >= 1/2)
@@ -157,7 +157,7 @@ __device__ __forceinline__ void item_f64(const Item& it, const Aux64* __restrict
     s.prod = e0;
     s.head = 1.0;
     s.dead = 0;
-    steps_f64<1, K>(s, U, sh, (ScalarGen)Z_u, (ScalarRows)rows_u, nodes, k, sp, (uint64_t)(p0 + lane));
+    steps_f64<1, K>(s, U, sh, (ScalarGen)Z_u, (ScalarRows)rows_u, nodes, k, sp, (uint32_t)(p0 + lane));
     if (p0 + lane <= p_last) {
 #pragma clang fp contract(off)
       acc_den += s.head;
