@@ -10,11 +10,11 @@ namespace {
 constexpr int size_of(int i) { return 2 * i + 2; }
 
 template <int... Is>
-hipError_t run(int kc, const InstDesc* insts, const RangeDesc* ranges, int n_ranges, int64_t n_items, const Aux32* aux32,
+hipError_t run(int kc, const InstDesc* insts, const RangeDesc* ranges, int n_ranges, ItemSpan span, const Aux32* aux32,
                const uint64_t* Z, double* sums, hipStream_t s, std::integer_sequence<int, Is...>) {
   hipError_t e = hipErrorInvalidValue;
   ((kc == size_of(Is)
-        ? (e = launch_f32_k<size_of(Is), false>(insts, ranges, n_ranges, n_items, aux32, Z, sums, s), 0)
+        ? (e = launch_f32_k<size_of(Is), false>(insts, ranges, n_ranges, span, aux32, Z, sums, s), 0)
         : 0),
    ...);
   return e;
@@ -22,9 +22,9 @@ hipError_t run(int kc, const InstDesc* insts, const RangeDesc* ranges, int n_ran
 
 }  // namespace
 
-hipError_t launch_qmc_f32_short(int kc, const InstDesc* insts, const RangeDesc* ranges, int n_ranges, int64_t n_items,
+hipError_t launch_qmc_f32_short(int kc, const InstDesc* insts, const RangeDesc* ranges, int n_ranges, ItemSpan span,
                           const Aux32* aux32, const uint64_t* Z, double* sums, hipStream_t s) {
-  return run(kc, insts, ranges, n_ranges, n_items, aux32, Z, sums, s, std::make_integer_sequence<int, 16>{});
+  return run(kc, insts, ranges, n_ranges, span, aux32, Z, sums, s, std::make_integer_sequence<int, 16>{});
 }
 
 }  // namespace vecchia

@@ -331,7 +331,7 @@ template <int K, bool BLOCK>
 __global__ __launch_bounds__(64 * kF32Waves) __attribute__((amdgpu_waves_per_eu(f32_min_waves(K)))) void qmc_f32(
     const InstDesc* __restrict__ insts, const RangeDesc* __restrict__ ranges, int n_ranges,
     const Aux32* __restrict__ aux32, const uint64_t* __restrict__ Zg, double* __restrict__ sums, int64_t item_base,
-    int64_t n_items, int items_per_wave) {
+    int64_t item_end, int items_per_wave) {
   __shared__ float4 cells[kQuantSlots];
   __shared__ uint64_t sh[kF32Waves][K > kF32AdvanceK ? K : 1];
   for (int e = threadIdx.x; e < kQuantSlots; e += 64 * kF32Waves)
@@ -339,26 +339,26 @@ __global__ __launch_bounds__(64 * kF32Waves) __attribute__((amdgpu_waves_per_eu(
   __syncthreads();
   const int wv = uniform(threadIdx.x >> 6);
   int64_t g = item_base + block_item(0) * (int64_t)(kF32Waves * items_per_wave) + wv;
-  for (int j = 0; j < items_per_wave && g < n_items; ++j, g += kF32Waves) {
+  for (int j = 0; j < items_per_wave && g < item_end; ++j, g += kF32Waves) {
     const Item it = decode_item(insts, ranges, n_ranges, g);
     item_f32<K, BLOCK>(it, aux32, Zg, sums, sh[wv], cells);
   }
 }
 
 template <int K, bool BLOCK>
-hipError_t launch_f32_k(const InstDesc* insts, const RangeDesc* ranges, int n_ranges, int64_t n_items,
+hipError_t launch_f32_k(const InstDesc* insts, const RangeDesc* ranges, int n_ranges, ItemSpan span,
                         const Aux32* aux32, const uint64_t* Z, double* sums, hipStream_t s) {
   // items per wave: up to 4 repay a workgroup's table load (8 KB, about 1 us)
   // while every compute unit still gets four rounds of workgroups
-  int64_t per = n_items / ((int64_t)kF32Waves * 8192);
+  int64_t per = (span.end - span.begin) / ((int64_t)kF32Waves * 8192);
   per = per < 1 ? 1 : per > 4 ? 4 : per;
   const int64_t block_items = kF32Waves * per;
   constexpr int64_t kMaxBlocks = kMaxLaunchThreads / (64 * kF32Waves);
-  for (int64_t b = 0; b < n_items; b += kMaxBlocks * block_items) {
-    const int64_t left = (n_items - b + block_items - 1) / block_items;
+  for (int64_t b = span.begin; b < span.end; b += kMaxBlocks * block_items) {
+    const int64_t left = (span.end - b + block_items - 1) / block_items;
     const unsigned n = (unsigned)(left < kMaxBlocks ? left : kMaxBlocks);
     hipLaunchKernelGGL((qmc_f32<K, BLOCK>), dim3(n), dim3(64 * kF32Waves), 0, s, insts, ranges, n_ranges, aux32, Z, sums,
-                       b, n_items, (int)per);
+                       b, span.end, (int)per);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

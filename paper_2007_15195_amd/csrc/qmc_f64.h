@@ -180,14 +180,14 @@ template <int K>
 __global__ __launch_bounds__(64 * f64_waves(K)) __attribute__((amdgpu_waves_per_eu(f64_waves(K) / 2))) void qmc_f64(
     const InstDesc* __restrict__ insts, const RangeDesc* __restrict__ ranges, int n_ranges,
     const Aux64* __restrict__ aux64, const uint64_t* __restrict__ Zg, double* __restrict__ sums, int64_t item_base,
-    int64_t n_items, int items_per_wave) {
+    int64_t item_end, int items_per_wave) {
   constexpr int W = f64_waves(K);
   __shared__ __align__(16) double nodes[2 * kNormNodes];
   __shared__ uint64_t sh[K > kF64AdvanceK ? W * K : 1];
   load_nodes(nodes);
   const int wv = uniform(threadIdx.x >> 6);
   int64_t g = item_base + block_item(0) * (int64_t)(W * items_per_wave) + wv;
-  for (int j = 0; j < items_per_wave && g < n_items; ++j, g += W) {
+  for (int j = 0; j < items_per_wave && g < item_end; ++j, g += W) {
     const Item it = decode_item(insts, ranges, n_ranges, g);
     item_f64<K>(it, aux64, Zg, sums, reinterpret_cast<const double*>(it.I->prep) + it.i * it.I->prep_stride, nodes,
                 sh + (K > kF64AdvanceK ? wv * K : 0));
@@ -257,20 +257,20 @@ __global__ __launch_bounds__(64 * f64_waves(K)) __attribute__((amdgpu_waves_per_
 }
 
 template <int K>
-hipError_t launch_f64_k(const InstDesc* insts, const RangeDesc* ranges, int n_ranges, int64_t n_items,
+hipError_t launch_f64_k(const InstDesc* insts, const RangeDesc* ranges, int n_ranges, ItemSpan span,
                         const Aux64* aux64, const uint64_t* Z, double* sums, hipStream_t s) {
   constexpr int W = f64_waves(K);
   // items per wave: enough to repay a workgroup's table load (about 2 us) while
   // every compute unit still gets four rounds of workgroups
   const int64_t most = K < 64 ? 64 / K : 1;
-  int64_t per = n_items / ((int64_t)W * 2048);
+  int64_t per = (span.end - span.begin) / ((int64_t)W * 2048);
   per = per < 1 ? 1 : per > most ? most : per;
   const int64_t block_items = W * per;
   const int64_t max_blocks = kMaxLaunchThreads / (64 * W);
-  for (int64_t b = 0; b < n_items; b += max_blocks * block_items) {
-    const int64_t left = (n_items - b + block_items - 1) / block_items;
+  for (int64_t b = span.begin; b < span.end; b += max_blocks * block_items) {
+    const int64_t left = (span.end - b + block_items - 1) / block_items;
     const unsigned n = (unsigned)(left < max_blocks ? left : max_blocks);
-    hipLaunchKernelGGL(qmc_f64<K>, dim3(n), dim3(64 * W), 0, s, insts, ranges, n_ranges, aux64, Z, sums, b, n_items,
+    hipLaunchKernelGGL(qmc_f64<K>, dim3(n), dim3(64 * W), 0, s, insts, ranges, n_ranges, aux64, Z, sums, b, span.end,
                        (int)per);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -237,6 +237,10 @@ Batch::~Batch() {
   if (d_ws_) hipFree(d_ws_);
 }
 
+// Work items (one wave each) from which a chain length gets a launch of its own:
+// two rounds of the device's 8192 wave slots.
+constexpr int64_t kMergeItems = 16384;
+
 static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 vecchia_status Batch::create(const std::vector<vecchia_plan_s*>& plans,
@@ -256,7 +260,7 @@ vecchia_status Batch::create(const std::vector<vecchia_plan_s*>& plans,
   b->prep_off_.resize(n);
   int64_t tb = 0, sb = 0;
   size_t prep = 0;
-  std::map<std::tuple<int, int, bool>, std::vector<RangeDesc>> by_k;   // (K, precision, block) -> ranges
+  std::map<std::tuple<int, bool, int>, std::vector<RangeDesc>> by_k;   // (precision, block, K) -> ranges
   for (int j = 0; j < n; ++j) {
     vecchia_plan_s* P = plans[j];
     std::string why;
@@ -320,7 +324,7 @@ vecchia_status Batch::create(const std::vector<vecchia_plan_s*>& plans,
         r.items_per_term = passes * R * C;
         r.n_chunks = C;
         // the FP64 kernels take plain and joint terms alike
-        by_k[{k, prec, prec == VECCHIA_FP32_LOOP && P->block > 0}].push_back(r);
+        by_k[{prec, prec == VECCHIA_FP32_LOOP && P->block > 0, k}].push_back(r);
       }
       i = e;
     }
@@ -334,28 +338,45 @@ vecchia_status Batch::create(const std::vector<vecchia_plan_s*>& plans,
   b->total_sums_ = sb;
   b->prep_bytes_ = prep;
   if (tb > 0x7fffffffLL) return set_error(VECCHIA_E_INVALID, "more than 2^31-1 terms in one batch");
-  // one launch per (K, precision); the launch with the most work runs on the
-  // caller's stream, the others (mostly the few terms with k < m) run beside it
-  for (auto it = by_k.begin(); it != by_k.end(); ++it) {
-    Launch L;
-    L.K = std::get<0>(it->first);
-    L.precision = std::get<1>(it->first);
-    L.block = std::get<2>(it->first);
-    L.range_off = (int)b->ranges_.size();
-    L.n_ranges = (int)it->second.size();
+  // Launches per (precision, joint or not), from the longest chains down: a
+  // length with fewer than kMergeItems work items (mostly the few terms with
+  // k < m) joins the launch of the next longer chains, whose kernel leaves a
+  // term's chain after its own k steps. Alone such a launch is a serial chain on
+  // a fraction of the device: about 10 us of gaps and, at 10^4 points, 60 us of
+  // latency each, one after another on the side streams (grid of 400 sites, m = 5:
+  // 107 -> 73 us a call). A length with more items keeps the kernel whose registers fit it.
+  // The launch with the most work runs on the caller's stream, the others beside it.
+  for (auto it = by_k.rbegin(); it != by_k.rend(); ++it) {
+    const int prec = std::get<0>(it->first), k = std::get<2>(it->first);
+    const bool block = std::get<1>(it->first);
     int64_t items = 0;
-    L.sov_steps = 0;
+    for (const RangeDesc& r : it->second) items += r.item_begin * r.items_per_term;
+    Launch* L = b->launches_.empty() ? nullptr : &b->launches_.back();
+    if (!L || L->precision != prec || L->block != block || items >= kMergeItems) {
+      Launch n;
+      n.K = k;
+      n.precision = prec;
+      n.block = block;
+      n.range_off = (int)b->ranges_.size();
+      n.n_ranges = 0;
+      n.n_items = n.sov_steps = 0;
+      b->launches_.push_back(n);
+      L = &b->launches_.back();
+    }
+    Span sp{k, {L->n_items, 0}, 0};
     for (RangeDesc r : it->second) {
       const int64_t nterms = r.item_begin;
-      r.item_begin = items;
-      items += nterms * r.items_per_term;
-      L.sov_steps += nterms * (int64_t)b->desc_[r.inst].passes * b->desc_[r.inst].n_shifts *
-                     b->desc_[r.inst].n_points * r.K;
+      r.item_begin = L->n_items;
+      L->n_items += nterms * r.items_per_term;
+      sp.sov_steps += nterms * (int64_t)b->desc_[r.inst].passes * b->desc_[r.inst].n_shifts *
+                      b->desc_[r.inst].n_points * r.K;
       b->ranges_.push_back(r);
+      ++L->n_ranges;
     }
-    L.n_items = items;
-    if (items > 0x7fffffffLL) return set_error(VECCHIA_E_INVALID, "more than 2^31-1 work items in one launch");
-    b->launches_.push_back(L);
+    sp.items.end = L->n_items;
+    L->sov_steps += sp.sov_steps;
+    L->spans.push_back(sp);
+    if (L->n_items > 0x7fffffffLL) return set_error(VECCHIA_E_INVALID, "more than 2^31-1 work items in one launch");
   }
   std::stable_sort(b->launches_.begin(), b->launches_.end(),
                    [](const Launch& a, const Launch& c) { return a.sov_steps * (a.precision == VECCHIA_FP64 ? 8 : 1) >
@@ -483,17 +504,23 @@ vecchia_status Batch::enqueue(hipStream_t s, bool allow_profile) {
   for (size_t li = 0; li < launches_.size() && e == hipSuccess; ++li) {
     const Launch& L = launches_[li];
     hipStream_t ls = (li == 0 || n_side == 0) ? s : side_[(li - 1) % n_side];
-    hipEvent_t a = nullptr, b = nullptr;
-    if (prof) {
+    auto qmc = [&](int K, ItemSpan span) {
+      return launch_qmc(K, L.precision, L.block, d_desc_, d_ranges_ + L.range_off, L.n_ranges, span, d_aux64_, d_aux32_,
+                        d_Z_, d_sums_, ls);
+    };
+    if (!prof) {
+      e = qmc(L.K, {0, L.n_items});
+      continue;
+    }
+    // timed: a launch per chain length, as vecchia_profile_read counts them
+    for (const Span& sp : L.spans) {
+      hipEvent_t a = nullptr, b = nullptr;
       e = profile_events(&a, &b);
       if (e == hipSuccess) e = hipEventRecord(a, ls);
+      if (e == hipSuccess) e = qmc(sp.K, sp.items);
+      if (e == hipSuccess) e = hipEventRecord(b, ls);
       if (e != hipSuccess) break;
-    }
-    e = launch_qmc(L.K, L.precision, L.block, d_desc_, d_ranges_ + L.range_off, L.n_ranges, L.n_items,
-                   d_aux64_, d_aux32_, d_Z_, d_sums_, ls);
-    if (prof && e == hipSuccess) {
-      e = hipEventRecord(b, ls);
-      profile_record(L.K, L.precision, a, b, L.sov_steps);
+      profile_record(sp.K, L.precision, a, b, sp.sov_steps);
     }
   }
   // join
@@ -715,7 +742,7 @@ vecchia_status Batch::time_main_launch(hipStream_t s, int reps, float* median_ms
   for (int r = 0; r < reps && e == hipSuccess; ++r) {
     e = hipEventRecord(ev[2 * r], s);
     if (e == hipSuccess)
-      e = launch_qmc(L.K, L.precision, L.block, d_desc_, d_ranges_ + L.range_off, L.n_ranges, L.n_items, d_aux64_,
+      e = launch_qmc(L.K, L.precision, L.block, d_desc_, d_ranges_ + L.range_off, L.n_ranges, L.spans[0].items, d_aux64_,
                      d_aux32_, d_Z_, d_sums_, s);
     if (e == hipSuccess) e = hipEventRecord(ev[2 * r + 1], s);
   }

@@ -87,14 +87,21 @@ class Batch {
   hipStream_t last_stream() const { return last_stream_; }
 
  private:
-  struct Launch {
+  // The items of one chain length within a launch.
+  struct Span {
     int K;
+    ItemSpan items;
+    int64_t sov_steps;   // sum over the span's terms of n_shifts * n_points * K
+  };
+  struct Launch {
+    int K;               // its longest chains
     int precision;
     bool block;
     int range_off;
     int n_ranges;
     int64_t n_items;
-    int64_t sov_steps;   // sum over the launch's terms of n_shifts * n_points * K
+    int64_t sov_steps;
+    std::vector<Span> spans;   // one per chain length, longest first
   };
   vecchia_status allocate();
   void carve(char* base);   // workspace arrays at base (the layout of create())

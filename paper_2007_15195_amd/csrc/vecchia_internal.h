@@ -131,9 +131,14 @@ hipError_t launch_setup(const InstDesc* d_insts, int n_inst, const int64_t* d_te
 hipError_t launch_setup_redo(const InstDesc* d_insts, int n_inst, const int64_t* d_term_bases, int max_vars,
                              Aux64* aux64, Aux32* aux32, const int32_t* list, const int64_t* count, int64_t cap,
                              hipStream_t s);
-// block: the launch's instances are block plans (denominator split per term).
+// A launch's items [begin, end) among those of its ranges.
+struct ItemSpan {
+  int64_t begin, end;
+};
+// K: the most SOV steps of any term of the span. block: the launch's instances
+// are block plans (denominator split per term).
 hipError_t launch_qmc(int K, int precision, bool block, const InstDesc* d_insts, const RangeDesc* d_ranges,
-                      int n_ranges, int64_t n_items, const Aux64* aux64, const Aux32* aux32,
+                      int n_ranges, ItemSpan span, const Aux64* aux64, const Aux32* aux32,
                       const uint64_t* d_Z, double* sums, hipStream_t s);
 // The handed-over terms of FP32 instances in FP64: a persistent grid takes
 // (term, item) pairs from a device-side list (ctr[0] entries, at most cap;
@@ -147,15 +152,15 @@ hipError_t launch_qmc_promoted(int K, const InstDesc* d_insts, int n_inst, const
 constexpr int kQmcShortK = 32;
 constexpr int qmc_kernel_size(int K) { return K >= kMaxM ? kMaxM : (K + 1) / 2 * 2; }
 constexpr int f32_block_kernel_size(int K) { return K > 60 ? kMaxM : (K + 3) / 4 * 4; }
-hipError_t launch_qmc_f32_short(int kc, const InstDesc* insts, const RangeDesc* ranges, int n_ranges, int64_t n_items,
+hipError_t launch_qmc_f32_short(int kc, const InstDesc* insts, const RangeDesc* ranges, int n_ranges, ItemSpan span,
                                 const Aux32* aux32, const uint64_t* Z, double* sums, hipStream_t s);
-hipError_t launch_qmc_f32_long(int kc, const InstDesc* insts, const RangeDesc* ranges, int n_ranges, int64_t n_items,
+hipError_t launch_qmc_f32_long(int kc, const InstDesc* insts, const RangeDesc* ranges, int n_ranges, ItemSpan span,
                                const Aux32* aux32, const uint64_t* Z, double* sums, hipStream_t s);
-hipError_t launch_qmc_f32_block(int kc, const InstDesc* insts, const RangeDesc* ranges, int n_ranges, int64_t n_items,
+hipError_t launch_qmc_f32_block(int kc, const InstDesc* insts, const RangeDesc* ranges, int n_ranges, ItemSpan span,
                                 const Aux32* aux32, const uint64_t* Z, double* sums, hipStream_t s);
-hipError_t launch_qmc_f64_short(int kc, const InstDesc* insts, const RangeDesc* ranges, int n_ranges, int64_t n_items,
+hipError_t launch_qmc_f64_short(int kc, const InstDesc* insts, const RangeDesc* ranges, int n_ranges, ItemSpan span,
                                 const Aux64* aux64, const uint64_t* Z, double* sums, hipStream_t s);
-hipError_t launch_qmc_f64_long(int kc, const InstDesc* insts, const RangeDesc* ranges, int n_ranges, int64_t n_items,
+hipError_t launch_qmc_f64_long(int kc, const InstDesc* insts, const RangeDesc* ranges, int n_ranges, ItemSpan span,
                                const Aux64* aux64, const uint64_t* Z, double* sums, hipStream_t s);
 hipError_t launch_qmc_promoted_short(int kc, const InstDesc* insts, int n_inst, const int64_t* term_bases,
                                      const Aux64* aux64, const uint64_t* Z, double* sums, const int32_t* list,
