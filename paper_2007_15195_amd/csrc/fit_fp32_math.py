@@ -4,7 +4,7 @@ fp32_math_coeffs.h next to this file.
 Two functions are approximated by ratios of polynomials:
 
   R = Phi(-a) exp(a^2/2) = erfcx(a / sqrt 2) / 2 as a function of v = kappa a,
-      kappa = sqrt(log2(e) / 2), for a in [0, 40]; degree (3, 4), positive
+      kappa = sqrt(log2(e) / 2), for a in [0, 40]; degree (4, 5), positive
       coefficients (the ratio decays like 1/(a sqrt(2 pi)) as the true R does).
       With v in hand, exp(-a^2/2) = 2^(-v^2), so the loop scales its rows by
       kappa once and never multiplies a^2 by log2(e)/2.
@@ -86,7 +86,7 @@ def main():
     kappa = float(mpmath.sqrt(1 / (2 * mpmath.log(2))))
     a = np.concatenate([np.linspace(0, 6, 1500), np.linspace(6, 40, 800)])
     ra = 0.5 * erfcx(a / np.sqrt(2.0))
-    eR, pR, qR = lawson(kappa * a, ra, 3, 4, 1.0 / ra)
+    eR, pR, qR = lawson(kappa * a, ra, 4, 5, 1.0 / ra, iters=300)
     aa = np.linspace(0, 40, 200001)
     rr = 0.5 * erfcx(aa / np.sqrt(2.0))
     eR32 = float(np.max(np.abs(eval_f32(pR, qR, np.float32(kappa) * aa) - rr) / rr))

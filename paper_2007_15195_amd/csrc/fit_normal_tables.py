@@ -13,8 +13,9 @@ z = -Phi^{-1}(q) on q in [2^-15, 1/2] as one quadratic per cell of 32 per
 octave, (c0, c1, c2, midpoint), minimax in absolute error, each coefficient
 rounded to FP32 before the lower ones are fitted; and the coefficients of
 log2 Phi(-v / kappa), v in [0, 4.7], kappa = sqrt(log2(e) / 2), a polynomial of
-degree 10 by Lawson's reweighted least squares: relative error of Phi up to
-v = 3.7 (Phi = 6.6e-6), absolute beyond. Its leading coefficient is negative, so
+degree 8 by Lawson's reweighted least squares: relative error of Phi up to
+v = 3.41 (Phi = 2^-15, below which the loop takes the ratio instead), absolute
+beyond. Its leading coefficient is negative, so
 2^poly falls to 0 beyond the fitted range.
 
 Run: python fit_normal_tables.py   (development-time only; the header is committed)
@@ -104,7 +105,7 @@ def cells32():
             yield c0, c1, c2, np.float32(mid)
 
 
-def tail_poly(n=10, vmax=4.7, vfull=3.7):
+def tail_poly(n=8, vmax=4.7, vfull=3.41):
     v = (1 - np.cos(np.linspace(0, np.pi, 1201))) / 2 * vmax
     g = np.array([float(mpmath.log(mpmath.ncdf(-mpmath.mpf(float(x)) / KAPPA), 2)) for x in v])
     w = np.maximum(np.minimum(1.0, 2.0 ** (g - np.interp(vfull, v, g))), 1e-9)

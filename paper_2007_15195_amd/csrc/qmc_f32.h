@@ -23,7 +23,7 @@
 // the quantile's cells 12, both beside the vector unit. So a step
 //  * takes the quantile from a table in LDS, one quadratic per 1/32 octave of
 //    q (2.9 clocks; log, sqrt, a ratio and its reciprocal took 16);
-//  * takes Phi(-|t|) as 2^p(|v|), a polynomial with literal coefficients (8.5;
+//  * takes Phi(-|t|) as 2^p(|v|), a polynomial with literal coefficients (7.3;
 //    the ratio, its reciprocal and an exponential took 11 to 14);
 //  * forms u = w e and 1 - u as em - wc em and m + wc em (wc = 1 - w), two FMAs
 //    whose smaller result is the quantile's argument;
@@ -32,7 +32,7 @@
 //    previous factor and the quantile again in the accurate split form below.
 // Measured over whole launches (8192 x 8 points, thresholds at 1.28), CU-clocks a
 // step now and with one-wave workgroups, fitted ratios and rows in LDS:
-// k = 10: 27.9 (38.8); k = 20: 33.1 (43.1); k = 31: 39.7 (56.7).
+// k = 10: 27.0 (38.8); k = 20: 31.8 (43.1); k = 31: 39.8 (56.7); k = 63: 57.7 (147).
 //
 // Rare lanes (cold32, cold32_first): factors are e = em * 2^en, with en = 0
 // except for lower-tail factors below 2^-60 (t < -9.1), which keep
@@ -48,8 +48,10 @@
 // step k (a scalar compare per step). The term's scaled rows come through scalar
 // loads as scalar operands: 1.05 clocks a coefficient, where LDS broadcasts took
 // 0.6 on the vector unit and 1.2 on the LDS pipe beside the table's gathers, 2.1
-// measured. A workgroup is four waves with their own items around one table
-// (8 KB), eight workgroups to a compute unit.
+// measured. (Two points per lane, sharing LDS row reads, take the coefficients'
+// cost down to 0.6 and the whole step not at all: 27.8 clocks against 27.0.) A
+// workgroup is four waves with their own items around one table (8 KB), eight
+// workgroups to a compute unit.
 #pragma once
 #include "vecchia_internal.h"
 
@@ -80,13 +82,11 @@ using ScalarRows32 = const __attribute__((address_space(4))) float*;
 #define VECCHIA_FMAMK(d, a, k, c) \
   __asm__("v_fmamk_f32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "i"(__builtin_bit_cast(uint32_t, (float)(k))), "v"(c))
 
-// Phi(-|v| / kappa) for |v| <= 3.7; beyond it falls to 0 with an absolute error
-// below 2e-11.
+// Phi(-|v| / kappa) for |v| <= 3.41 (Phi >= 2^-15); beyond it falls to 0 with an
+// absolute error below 5e-11.
 __device__ __forceinline__ float tail_f32(float v) {
   const float a = fabsf(v);
-  float p = kTailPoly[10];
-  VECCHIA_FMAAK(p, a, kTailPoly[9]);
-  VECCHIA_FMAAK(p, a, kTailPoly[8]);
+  float p = kTailPoly[8];
   VECCHIA_FMAAK(p, a, kTailPoly[7]);
   VECCHIA_FMAAK(p, a, kTailPoly[6]);
   VECCHIA_FMAAK(p, a, kTailPoly[5]);
@@ -103,10 +103,12 @@ __device__ __forceinline__ PhiParts phi_f32_lit(float v) {
   const float a = fabsf(v);
   PhiParts o;
   o.f = -(v * v);
-  float p = kRP[3], q = kRQ[4];
+  float p = kRP[4], q = kRQ[5];
+  VECCHIA_FMAAK(p, a, kRP[3]);
   VECCHIA_FMAAK(p, a, kRP[2]);
   VECCHIA_FMAAK(p, a, kRP[1]);
   VECCHIA_FMAAK(p, a, kRP[0]);
+  VECCHIA_FMAAK(q, a, kRQ[4]);
   VECCHIA_FMAAK(q, a, kRQ[3]);
   VECCHIA_FMAAK(q, a, kRQ[2]);
   VECCHIA_FMAAK(q, a, kRQ[1]);
@@ -159,7 +161,7 @@ __device__ __noinline__ float cold32_first(float em, float en, float ec, bool ne
 
 template <int K>
 struct Chain32 {
-  float y[K];
+  float y[K];      // -y (the recursion then adds, in the short FMA encoding)
   float em, m;     // the latest factor and 1 - it (or Phi(-|t|))
   float v;         // its argument, kappa t
   float qm;        // product of factors, qm 2^qe
@@ -188,11 +190,12 @@ __device__ __forceinline__ void steps_f32(Chain32<K>& s, uint64_t* U, const uint
   wc = fabsf(wc);
   const float um = fmaf(-wc, s.em, s.em);              // u = w e
   const float qt = fminf(um, fmaf(wc, s.em, s.m));     // min(u, 1 - u)
-  float y = __builtin_copysignf(quant_f32(cells, qt), um - 0.5f);
-  const bool rare = !(qt >= kQuantMin) || (A == 1 && split0);
+  float y = __builtin_copysignf(quant_f32(cells, qt), 0.5f - um);
+  bool rare = !(qt >= kQuantMin);
+  if (A == 1) rare = rare || split0;
   if (__builtin_expect(any_lane(rare), 0)) {
     if constexpr (A == 1) {
-      if (rare) y = cold32_first(ax.em0, ax.en0, ax.ec0, ax.neg0 != 0.0f, wc);
+      if (rare) y = -cold32_first(ax.em0, ax.en0, ax.ec0, ax.neg0 != 0.0f, wc);
     } else {
       s.qe += __builtin_amdgcn_frexp_expf(s.qm);
       s.qm = __builtin_amdgcn_frexp_mantf(s.qm);
@@ -200,7 +203,7 @@ __device__ __forceinline__ void steps_f32(Chain32<K>& s, uint64_t* U, const uint
         const Cold32 c = cold32(s.v, wc);
         s.em = c.em;
         s.qe += (int)c.en;
-        y = c.y;
+        y = -c.y;
       }
     }
   }
@@ -222,7 +225,7 @@ __device__ __forceinline__ void steps_f32(Chain32<K>& s, uint64_t* U, const uint
   constexpr int ro = A * (A + 1) / 2;
   float v = rows[ro + A];
 #pragma unroll
-  for (int c = 0; c < A; ++c) v = fmaf(-rows[ro + c], s.y[c], v);
+  for (int c = 0; c < A; ++c) v = fmaf(rows[ro + c], s.y[c], v);
   s.v = v;
   if constexpr (A < K) {
     if (A == k) return;
@@ -295,7 +298,8 @@ __device__ __forceinline__ void item_f32(const Item& it, const Aux32* __restrict
     const PhiParts ph = phi_f32_lit(s.v);
     double em = (double)ph.em, ec = (double)(ph.neg ? 1.0f - ph.em : ph.m);
     double den = (double)(BLOCK ? s.dm : s.qm), num = (double)s.qm;
-    if (__builtin_expect(any_lane(s.v < -kDeepV || s.qe != 0 || (BLOCK && s.de != 0)), 0)) {
+    const uint64_t odd = __builtin_amdgcn_ballot_w64(s.v < -kDeepV) | __builtin_amdgcn_ballot_w64((s.qe | s.de) != 0);
+    if (__builtin_expect(odd != 0, 0)) {
       if (s.v < -kDeepV) {
         const float f = fmaxf(ph.f, -1048576.0f), fl = floorf(f);
         em = ldexp((double)(fast_exp2(f - fl) * ph.R), (int)fl);
