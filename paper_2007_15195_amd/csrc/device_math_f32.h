@@ -50,13 +50,17 @@ __device__ __forceinline__ float ninv_tail_from_log2_split(float lq2) {
   float q = kZQ[4];
 #pragma unroll
   for (int c = 3; c >= 0; --c) q = fmaf(q, s, kZQ[c]);
-  float pw = kZPW[3];
+  float z = p * fast_rcp(q);
+  if (__builtin_amdgcn_ballot_w64(s > 34.0f) != 0) {   // skipped by waves with no such lane
+    float pw = kZPW[3];
 #pragma unroll
-  for (int c = 2; c >= 0; --c) pw = fmaf(pw, s, kZPW[c]);
-  float qw = kZQW[2];
+    for (int c = 2; c >= 0; --c) pw = fmaf(pw, s, kZPW[c]);
+    float qw = kZQW[2];
 #pragma unroll
-  for (int c = 1; c >= 0; --c) qw = fmaf(qw, s, kZQW[c]);
-  return s > 34.0f ? pw * fast_rcp(qw) : p * fast_rcp(q);
+    for (int c = 1; c >= 0; --c) qw = fmaf(qw, s, kZQW[c]);
+    if (s > 34.0f) z = pw * fast_rcp(qw);
+  }
+  return z;
 }
 
 // Phi(t) from v = kappa t, as e = em (exact unless em is split further by the

@@ -34,9 +34,10 @@
 // step now and with one-wave workgroups, fitted ratios and rows in LDS:
 // k = 10: 27.0 (38.8); k = 20: 31.8 (43.1); k = 31: 39.8 (56.7); k = 63: 57.7 (147).
 //
-// Rare lanes (cold32, cold32_first): factors are e = em * 2^en, with en = 0
-// except for lower-tail factors below 2^-60 (t < -9.1), which keep
-// 2^floor(-v^2) in en so that em stays in [R, 2R). The product of the factors is
+// Rare lanes (cold32, cold32_first; 0.4% of wave-steps with thresholds near the
+// 0.9 quantile, up to 20% with rough thresholds on a smooth field): factors are
+// e = em * 2^en, with en = 0 except for a rare lane's lower-tail factors, which
+// keep 2^floor(-v^2) in en so that em stays in [R, 2R). The product of the factors is
 // qm * 2^qe (qe an integer): a common factor is at least 2^-15, so qm is
 // renormalised every fourth step where it fell below 2^-50, and around every
 // rare step; it never leaves the normal range. The last factor of a chain, whose
@@ -76,7 +77,9 @@ constexpr int f32_min_waves(int K) { return K <= 12 ? 8 : K <= 18 ? 6 : K <= 24 
 using ScalarGen32 = const __attribute__((address_space(4))) uint64_t*;
 using ScalarRows32 = const __attribute__((address_space(4))) float*;
 
-// p * a + literal and a * literal + c, the coefficients in the instruction.
+// p * a + literal and a * literal + c, the coefficients in the instruction. No
+// operand may come straight from exp, log, rcp or sqrt: the wait state that
+// gfx950 wants behind those is not inserted before inline assembly.
 #define VECCHIA_FMAAK(p, a, k)                                                                                      \
   __asm__("v_fmaak_f32 %0, %1, %2, %3" : "=v"(p) : "v"(p), "v"(a), "i"(__builtin_bit_cast(uint32_t, (float)(k))))
 #define VECCHIA_FMAMK(d, a, k, c) \
@@ -99,10 +102,9 @@ __device__ __forceinline__ float tail_f32(float v) {
 }
 
 // phi_f32 with the ratio's coefficients in the instructions.
-__device__ __forceinline__ PhiParts phi_f32_lit(float v) {
+__device__ __forceinline__ float ratio_f32(float v, float* f) {
   const float a = fabsf(v);
-  PhiParts o;
-  o.f = -(v * v);
+  *f = -(v * v);
   float p = kRP[4], q = kRQ[5];
   VECCHIA_FMAAK(p, a, kRP[3]);
   VECCHIA_FMAAK(p, a, kRP[2]);
@@ -113,7 +115,11 @@ __device__ __forceinline__ PhiParts phi_f32_lit(float v) {
   VECCHIA_FMAAK(q, a, kRQ[2]);
   VECCHIA_FMAAK(q, a, kRQ[1]);
   VECCHIA_FMAAK(q, a, kRQ[0]);
-  o.R = p * fast_rcp(q);
+  return p * fast_rcp(q);
+}
+__device__ __forceinline__ PhiParts phi_f32_lit(float v) {
+  PhiParts o;
+  o.R = ratio_f32(v, &o.f);
   o.m = fast_exp2(o.f) * o.R;
   o.neg = v <= 0.0f;
   o.em = o.neg ? o.m : 1.0f - o.m;
@@ -129,25 +135,27 @@ __device__ __forceinline__ float quant_f32(const float4* cells, float q) {
 }
 
 struct Cold32 {
-  float em, en, y;   // the previous factor em * 2^en and y = Phi^{-1}(w em 2^en)
+  float em, en, y;   // the previous factor em * 2^en and -Phi^{-1}(w em 2^en)
 };
 
-// A rare lane's step: the previous factor from its v, and the quantile of w times it.
+// A rare lane's step: the previous factor from its v, and the quantile of w times
+// it. A lower-tail factor keeps 2^floor(-v^2) in en (bounded, so that the sum of
+// exponents cannot overflow). Out of line: inlined it is 3% faster where a fifth
+// of the wave-steps are rare and k = 20, and 2.5% slower at k = 50.
 __device__ __noinline__ Cold32 cold32(float v, float awc) {
-  const PhiParts ph = phi_f32(v);
+  float f, R = ratio_f32(v, &f);
+  f = fmaxf(f, -1048576.0f);
+  const float fl = floorf(f);
+  const float mm = fast_exp2(f - fl) * R;
+  const bool neg = v <= 0.0f;
+  const float m = ldexpf(mm, (int)fl);
   Cold32 o;
-  o.em = ph.em;
-  o.en = 0.0f;
-  if (v < -kDeepV) {
-    // exponent kept outside the float (bounded so that the sum of exponents cannot overflow)
-    const float f = fmaxf(ph.f, -1048576.0f), fl = floorf(f);
-    o.em = fast_exp2(f - fl) * ph.R;
-    o.en = fl;
-  }
+  o.em = neg ? mm : 1.0f - m;
+  o.en = neg ? fl : 0.0f;
   const float um = fmaf(-awc, o.em, o.em);
-  const bool lower = ph.neg || um <= 0.5f;
-  const float z = ninv_tail_from_log2_split(fast_log2(lower ? um : fmaf(awc, o.em, ph.m)) + o.en);
-  o.y = lower ? -z : z;
+  const bool lower = neg || um <= 0.5f;
+  const float z = ninv_tail_from_log2_split(fast_log2(lower ? um : fmaf(awc, o.em, m)) + o.en);
+  o.y = lower ? z : -z;
   return o;
 }
 
@@ -156,7 +164,7 @@ __device__ __noinline__ float cold32_first(float em, float en, float ec, bool ne
   const float um = fmaf(-awc, em, em);
   const bool lower = neg || um <= 0.5f;
   const float z = ninv_tail_from_log2_split(fast_log2(lower ? um : fmaf(awc, em, ec)) + en);
-  return lower ? -z : z;
+  return lower ? z : -z;
 }
 
 template <int K>
@@ -195,7 +203,7 @@ __device__ __forceinline__ void steps_f32(Chain32<K>& s, uint64_t* U, const uint
   if (A == 1) rare = rare || split0;
   if (__builtin_expect(any_lane(rare), 0)) {
     if constexpr (A == 1) {
-      if (rare) y = -cold32_first(ax.em0, ax.en0, ax.ec0, ax.neg0 != 0.0f, wc);
+      if (rare) y = cold32_first(ax.em0, ax.en0, ax.ec0, ax.neg0 != 0.0f, wc);
     } else {
       s.qe += __builtin_amdgcn_frexp_expf(s.qm);
       s.qm = __builtin_amdgcn_frexp_mantf(s.qm);
@@ -203,7 +211,7 @@ __device__ __forceinline__ void steps_f32(Chain32<K>& s, uint64_t* U, const uint
         const Cold32 c = cold32(s.v, wc);
         s.em = c.em;
         s.qe += (int)c.en;
-        y = -c.y;
+        y = c.y;
       }
     }
   }
