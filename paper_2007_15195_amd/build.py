@@ -49,8 +49,10 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-Wall", "-Wno
 
 
 # Per-file flags. fullsov.hip: MFMA accumulators stay in VGPRs (gfx950 takes
-# them there), so the product loop carries no accumulator copies.
-EXTRA = {"fullsov.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+# them there), so the product loop carries no accumulator copies; and constants
+# are not hoisted out of the loops over dimensions, where they would take the
+# registers of the recursion and be reloaded from scratch memory at every step.
+EXTRA = {"fullsov.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-mllvm", "-disable-machine-licm"]}
 
 
 def _compile(src: str) -> str:

@@ -3,22 +3,15 @@
 // against (Section 3.1, Figures 1-4), on the plan's ordering and covariance.
 //
 //   1. full_cov_build: the dense D x D covariance (plan order, FP64) and b = x / scale;
-//   2. blocked right-looking Cholesky, block 32: chol_diag (one wave, rows in registers),
-//      chol_panel (one thread per row below the block), chol_update (64 x 64
-//      tiles of the trailing lower triangle on the FP64 matrix cores);
-//   3. chol_mirror copies L into the upper triangle (L^T), so that a column of L
-//      is contiguous;
-//   4. full_sov: one workgroup per 16 to 64 consecutive lattice points of one
-//      shift (16 per wave) for the whole chain; dimensions advance in blocks of
-//      64. The part of each block's limits that comes from earlier dimensions,
-//      b_a - sum_{c<j0} L_ac y_c, is a product of 64 rows of L by the earlier y
-//      of the workgroup's points, run on the FP64 matrix cores
-//      (v_mfma_f64_16x16x4); the block's own recursion then runs from LDS in
-//      each wave (its four 16-lane groups evaluate the same 16 points, and each
-//      group updates every fourth later row):
-//          e_a = Phi(t_a), log prod += log Phi(t_a), y_a = Phi^-1(max(w_a e_a, DBL_MIN)).
-//      Each wave leaves {max, sum exp(. - max)} of its points' log products;
-//   5. full_final (one workgroup, fixed-order trees): per shift l_r = log mean
+//   2. blocked right-looking Cholesky, one launch per 32 columns (chol_step):
+//      the panel's factor, its rows and the update of the trailing lower
+//      triangle on the FP64 matrix cores; the factor goes to the upper triangle
+//      as L^T, so that a column of L is contiguous;
+//   3. full_sov: one workgroup per 16 to 144 lattice points for the whole chain:
+//      products by the earlier dimensions' y on the FP64 matrix cores
+//      (v_mfma_f64_16x16x4), the recursion of 16 dimensions at a time with a
+//      point per lane; it leaves {max, sum exp(. - max)} of each 16 points' log products;
+//   4. full_final (one workgroup, fixed-order trees): per shift l_r = log mean
 //      over points, then log F = log mean_r exp(l_r) and the delta-method SE
 //      over the shifts.
 // Lattice: Z_j from the first D - 1 primes; the shift of dimension j in
@@ -32,6 +25,7 @@
 #include "device_cov.h"
 #include "device_math_f64.h"
 #include "lattice.h"
+#include "qmc_f64.h"
 #include "runtime.h"
 #include "vecchia.h"
 
@@ -39,8 +33,10 @@ namespace vecchia {
 namespace {
 
 constexpr int kCholB = 32;     // Cholesky block
-constexpr int kFsB = 64;       // SOV dimension block
 constexpr int kFsWavePts = 16; // lattice points per wave (one MFMA column tile)
+constexpr int kFsTile = 16;    // dimensions per tile (one MFMA row tile)
+constexpr int kFsWaves = 8;    // waves per workgroup: row tiles per block of dimensions
+constexpr int kFsBufs = 4;        // product steps in flight, less one
 
 // v_mfma_f64_16x16x4f64, D = A B + C with A 16 x 4, B 4 x 16: lane l supplies
 // A[l % 16][l / 16] and B[l / 16][l % 16], and holds D[4 e + l / 16][l % 16] in
@@ -76,79 +72,115 @@ __global__ __launch_bounds__(256) void full_cov_build(CovArgs a, int64_t D, doub
   if (j == 0) b[i] = a.x[a.perm[i]] * a.inv_scale;
 }
 
-// Factor the diagonal block [k0, k0 + n) in place (one wave; right-looking,
-// lane r holds row r of the block in registers). Column j's pivot is broadcast
-// from lane j, the column goes through LDS, and each lane updates its own row
-// with independent FMAs. A non-positive pivot writes NaN on the diagonal.
-__global__ __launch_bounds__(64) void chol_diag(double* __restrict__ A, int64_t D, int64_t k0, int n) {
-  __shared__ double col[kCholB];
-  const int lane = threadIdx.x;
-  double c[kCholB];
-#pragma unroll
-  for (int p = 0; p < kCholB; ++p) c[p] = (lane < n && p <= lane) ? A[(k0 + lane) * D + k0 + p] : 0.0;
-#pragma unroll
-  for (int j = 0; j < kCholB; ++j) {
-    if (j < n) {
-      const double d = __shfl(c[j], j, 64);
-      const double ljj = d > 0.0 ? sqrt(d) : __builtin_nan("");
-      c[j] = lane > j ? c[j] / ljj : (lane == j ? ljj : c[j]);
-      if (lane < kCholB) col[lane] = c[j];
-      __syncthreads();
-#pragma unroll
-      for (int p = j + 1; p < kCholB; ++p)
-        if (p <= lane) c[p] -= c[j] * col[p];
-      __syncthreads();   // every lane has read the column before the next one is written
-    }
-  }
-#pragma unroll
-  for (int p = 0; p < kCholB; ++p)
-    if (lane < n && p <= lane) A[(k0 + lane) * D + k0 + p] = c[p];
+__device__ __forceinline__ double lane_value(double v, int lane) {   // lane uniform
+  const uint64_t b = bits_of(v);
+  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)b, lane);
+  const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(b >> 32), lane);
+  return of_bits(((uint64_t)hi << 32) | lo);
 }
 
-// Rows i >= k0 + n: L[i, k0:k0+n] = A[i, k0:k0+n] L_kk^-T (forward substitution).
-__global__ __launch_bounds__(256) void chol_panel(double* __restrict__ A, int64_t D, int64_t k0, int n) {
-  __shared__ double Lk[kCholB][kCholB + 1];
-  for (int idx = threadIdx.x; idx < n * n; idx += 256) {
-    const int r = idx / n, c = idx - r * n;
-    Lk[r][c] = c <= r ? A[(k0 + r) * D + k0 + c] : 0.0;
-  }
-  __syncthreads();
-  const int64_t i = k0 + n + (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= D) return;
-  double* row = A + i * D + k0;
-  double xr[kCholB];
-#pragma unroll
-  for (int c = 0; c < kCholB; ++c) {
-    if (c < n) {
-      double v = row[c];
-#pragma unroll
-      for (int d = 0; d < c; ++d) v -= xr[d] * Lk[c][d];
-      xr[c] = v / Lk[c][c];
-      row[c] = xr[c];
-    }
-  }
-}
-
-// Trailing update of the lower triangle: A[i][j] -= sum_c L[i][k0+c] L[j][k0+c]
-// for k0 + n <= j <= i, in 64 x 64 tiles (tiles above the diagonal exit). The
-// tile's two panels are staged in LDS column-major (Pt[c][row], zero past the
-// panel or the matrix), and each of the four waves takes a 32 x 32 quarter as
-// 2 x 2 tiles of v_mfma_f64_16x16x4 over the panel's kCholB columns.
-__global__ __launch_bounds__(256) void chol_update(double* __restrict__ A, int64_t D, int64_t k0, int n) {
+// One step of the blocked right-looking Cholesky of the lower triangle, a launch
+// per panel of kCholB columns: workgroup (tj, ti), tj <= ti, of 64 x 64 tiles of
+// the trailing matrix [k0 + n, D).
+//   1. Wave 0 factors the panel's diagonal block (lane r holds row r in
+//      registers; a column's pivot and entries are read across lanes as scalar
+//      operands) while the other waves stage the panel rows of the tile's rows
+//      and columns in LDS.
+//   2. One thread per staged row solves x L_kk^T = a (the pivots' reciprocals
+//      from step 1, updates of the row's later entries independent of each other).
+//   3. The tile is updated, A[i][j] -= sum_c x_i[c] x_j[c], each wave a 32 x 32
+//      quarter as 2 x 2 tiles of v_mfma_f64_16x16x4.
+// Every workgroup repeats steps 1 and 2 for its own tile: both are latency, and
+// repeating them costs less than the two launches that would share them (and a
+// factor written in place would be read by workgroups that have not started).
+// The factor goes to the upper triangle as L^T, its diagonal's reciprocal to
+// dinv; the lower triangle is left with the panels as they were before their
+// own step. A non-positive pivot gives NaN from its column on. Bounded by the
+// chain of launches: 26 us each at 2,500 dimensions, 79 of them, against 50 us
+// for the three launches (factor, rows, update) of a panel before. (The factor's
+// rows by LDS broadcasts instead of lane reads: 31 us, its registers spill.)
+__global__ __launch_bounds__(256) void chol_step(double* __restrict__ A, double* __restrict__ dinv, int64_t D,
+                                                 int64_t k0, int n) {
   const int64_t base = k0 + n;
   const int64_t ti = blockIdx.y, tj = blockIdx.x;
   if (tj > ti) return;
-  __shared__ double Pi[kCholB][64 + 1], Pj[kCholB][64 + 1];
-  for (int idx = threadIdx.x; idx < 64 * kCholB; idx += 256) {
-    const int r = idx / kCholB, c = idx - r * kCholB;
-    const int64_t ri = base + ti * 64 + r, rj = base + tj * 64 + r;
-    Pi[c][r] = (c < n && ri < D) ? A[ri * D + k0 + c] : 0.0;
-    Pj[c][r] = (c < n && rj < D) ? A[rj * D + k0 + c] : 0.0;
-  }
-  __syncthreads();
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  __shared__ double P[128][kCholB + 1];          // panel rows: 0..63 the tile's rows, 64..127 its columns
+  __shared__ double Lc[kCholB][kCholB];          // L_kk by columns: Lc[c][r]
+  __shared__ double inv[kCholB];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int wi = wv >> 1, wj = wv & 1;
   const int m = lane & 15, kq = lane >> 4;
+  const int64_t i0 = base + ti * 64, c0 = base + tj * 64;
+  if (wv == 0) {
+    double c[kCholB];
+#pragma unroll
+    for (int p = 0; p < kCholB; ++p) c[p] = (lane < n && p <= lane) ? A[(k0 + lane) * D + k0 + p] : 0.0;
+#pragma unroll
+    for (int j = 0; j < kCholB; ++j) {
+      if (j < n) {
+        const double d = lane_value(c[j], j);
+        // 1 / sqrt(d) by two Newton steps, then sqrt(d) = d / sqrt(d) corrected
+        double r = __builtin_amdgcn_rsq(d);
+        r = __builtin_fma(r, __builtin_fma(-d * r, 0.5 * r, 0.5), r);
+        r = __builtin_fma(r, __builtin_fma(-d * r, 0.5 * r, 0.5), r);
+        double g = d * r;
+        g = __builtin_fma(__builtin_fma(-g, g, d), 0.5 * r, g);
+        if (!(d > 0.0)) r = g = __builtin_nan("");
+        c[j] = lane == j ? g : c[j] * r;
+        if (lane == j) inv[j] = r;
+        if (lane >= j && lane < kCholB) Lc[j][lane] = c[j];
+#pragma unroll
+        for (int p = j + 1; p < kCholB; ++p) c[p] = __builtin_fma(-lane_value(c[j], p), c[j], c[p]);
+      }
+    }
+    if (ti == 0) {
+#pragma unroll
+      for (int j = 0; j < kCholB; ++j)
+        if (j < n && lane > j && lane < n) A[(k0 + j) * D + k0 + lane] = c[j];
+      if (lane < n) dinv[k0 + lane] = inv[lane];
+    }
+  } else {
+    // rows past the matrix as zeros: their products are never stored
+    for (int idx = tid - 64; idx < 128 * kCholB; idx += 192) {
+      const int r = idx / kCholB, c = idx - r * kCholB;
+      const int64_t row = r < 64 ? i0 + r : c0 + r - 64;
+      P[r][c] = row < D ? A[row * D + k0 + c] : 0.0;
+    }
+  }
+  // the tile, while the factor is under way
+  double tile[2][2][4];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int64_t i = i0 + 32 * wi + 16 * a + 4 * e + kq, j = c0 + 32 * wj + 16 * b + m;
+        tile[a][b][e] = (i < D && j <= i) ? A[i * D + j] : 0.0;
+      }
+  if (base >= D) return;   // the last panel: nothing below it (uniform over the grid)
+  __syncthreads();
+  if (tid < (ti == tj ? 64 : 128)) {
+    double x[kCholB];
+#pragma unroll
+    for (int c = 0; c < kCholB; ++c) x[c] = P[tid][c];
+#pragma unroll
+    for (int c = 0; c < kCholB; ++c) {
+      x[c] *= inv[c];
+#pragma unroll
+      for (int d = c + 1; d < kCholB; ++d) x[d] = __builtin_fma(-Lc[c][d], x[c], x[d]);
+    }
+#pragma unroll
+    for (int c = 0; c < kCholB; ++c) P[tid][c] = x[c];
+  }
+  __syncthreads();
+  if (tj == 0) {
+    for (int idx = tid; idx < 64 * kCholB; idx += 256) {
+      const int c = idx >> 6, r = idx & 63;
+      if (i0 + r < D) A[(k0 + c) * D + i0 + r] = P[r][c];
+    }
+  }
+  const double (*Pj)[kCholB + 1] = ti == tj ? P : P + 64;
   fs_d4 acc[2][2];
 #pragma unroll
   for (int a = 0; a < 2; ++a)
@@ -157,8 +189,8 @@ __global__ __launch_bounds__(256) void chol_update(double* __restrict__ A, int64
 #pragma unroll
   for (int ks = 0; ks < kCholB / 4; ++ks) {
     const int c = 4 * ks + kq;
-    const double a0 = Pi[c][32 * wi + m], a1 = Pi[c][32 * wi + 16 + m];
-    const double b0 = Pj[c][32 * wj + m], b1 = Pj[c][32 * wj + 16 + m];
+    const double a0 = P[32 * wi + m][c], a1 = P[32 * wi + 16 + m][c];
+    const double b0 = Pj[32 * wj + m][c], b1 = Pj[32 * wj + 16 + m][c];
     acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc[0][0], 0, 0, 0);
     acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, acc[0][1], 0, 0, 0);
     acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc[1][0], 0, 0, 0);
@@ -172,188 +204,297 @@ __global__ __launch_bounds__(256) void chol_update(double* __restrict__ A, int64
     for (int b = 0; b < 2; ++b)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int64_t i = base + ti * 64 + 32 * wi + 16 * a + 4 * e + kq;
-        const int64_t j = base + tj * 64 + 32 * wj + 16 * b + m;
-        if (i < D && j <= i) A[i * D + j] -= acc[a][b][e];
+        const int64_t i = i0 + 32 * wi + 16 * a + 4 * e + kq, j = c0 + 32 * wj + 16 * b + m;
+        if (i < D && j <= i) A[i * D + j] = tile[a][b][e] - acc[a][b][e];
       }
 }
 
-// Upper triangle := L^T (A[j][i] = A[i][j] for j < i), 32 x 32 tiles through LDS.
-__global__ __launch_bounds__(256) void chol_mirror(double* __restrict__ A, int64_t D) {
-  const int64_t ti = blockIdx.y, tj = blockIdx.x;
-  if (tj > ti) return;
-  __shared__ double T[32][33];
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;   // 32 x 8
-  for (int r = ty; r < 32; r += 8) {
-    const int64_t i = ti * 32 + r, j = tj * 32 + tx;
-    T[r][tx] = (i < D && j < D && j < i) ? A[i * D + j] : 0.0;
-  }
-  __syncthreads();
-  for (int r = ty; r < 32; r += 8) {
-    const int64_t j = tj * 32 + r, i = ti * 32 + tx;   // write A[j][i] = L[i][j]
-    if (i < D && j < D && j < i) A[j * D + i] = T[tx][r];
-  }
+// log Phi(t), t < -kPhiNodeMax (or NaN), with e = Phi(t): log e while e is above
+// 1e-197; below, -t^2/2 + log((1 - 1/t^2 + 1*3/t^4 - ...) / (|t| sqrt(2 pi))), whose
+// first term left out is 3e-16 at t = -30.
+__device__ __forceinline__ double log_ncdf_low(double t, double e) {
+  const double h = t * t, z = div64(1.0, h);
+  double p = 1.0 - 13.0 * z;
+#pragma unroll
+  for (int k = 11; k >= 1; k -= 2) p = __builtin_fma(-k * z, p, 1.0);
+  const bool far = !(t > -30.0);
+  return log64(far ? div64(p, -2.50662827463100050242 * t) : e) - (far ? 0.5 * h : 0.0);
 }
 
-__device__ __forceinline__ double log_ncdf(double t) {
-  return t < 0.0 ? log(0.5 * erfcx(-t * 0.70710678118654752440)) - 0.5 * t * t
-                 : log1p(-0.5 * erfc(t * 0.70710678118654752440));
-}
-
-// The FP64 normal CDF and quantile of device_math_f64.h, both out of line:
-// inlined into the recursion they would take registers the product loop needs.
-__device__ __noinline__ double ncdf_full(double t) { return phi64(t); }
-__device__ __noinline__ double ncdfinv_full(double u) { return ninv64(u); }
-
-// L: D x D with L in the lower triangle and L^T in the upper; b: D limits;
-// Z: D - 1 generators; Y: (D - 1) x S (S = N R), the y of every point,
-// dimension-major; part: R x gridDim.x partial {max, sum exp}.
-struct SovSizes {
-  int64_t D, N, S;
+// L: D x D with L^T strictly above the diagonal (what is on and below it is not
+// read as L); dinv: reciprocals of L's diagonal; b: D limits; Z: D - 1 generators;
+// Y: per workgroup, earlier step of four dimensions and tile of 16 points, 64 y
+// (dimension 4 s + lane / 16 of point lane % 16); part: {max, sum exp} per tile of points.
+struct SovArgs {
+  const double* L;
+  const double* dinv;
+  const double* b;
+  const uint64_t* Z;
+  double* Y;
+  double2* part;
+  int64_t D, N;
   uint64_t seed;
+  int64_t tiles, all_tiles;   // 16-point tiles per shift, and of all shifts
+  int64_t y_steps;            // steps of four dimensions in a workgroup's Y
 };
 
-// Each wave owns 16 consecutive lattice points of one shift (blockIdx.y) for the
-// whole chain, and a workgroup holds NW such waves; dimensions advance in
-// blocks of kFsB. A wave depends only on its own points' y:
-//  * Earlier dimensions: T[q][p] = b_{j0+q} - sum_{c<j0} L[j0+q][c] y_c[p] is a
-//    (kFsB x j0) by (j0 x 16) product, taken as four 16 x 16 tiles of
-//    v_mfma_f64_16x16x4: the A operand is L[j0 + 16 i + m][c0 + k] (row c0 + k
-//    of the mirrored upper triangle, 16 consecutive doubles per k), the B
-//    operand y_{c0 + k} of the wave's 16 points (16 consecutive doubles of Y);
-//    four MFMAs per step of 4, the next step's loads issued before them.
-//  * The block itself: T goes to the wave's LDS slice and the wave runs the
-//    recursion right-looking over the block's rows (the block's triangle of L
-//    staged in LDS once per workgroup); lane group g = lane / 16 updates the
-//    rows q' = q + 1 + g, q + 5 + g, ... of the wave's 16 points:
-//        e = Phi(t_q), log prod += log Phi(t_q), y_q = Phi^-1(max(w_q e, DBL_MIN)),
-//        T[q'] -= L[j0 + q'][j0 + q] y_q for q' > q.
-// Two workgroup barriers per block guard the shared triangle; the wave's own y
-// (global) and T (LDS) need only its own ordering.
-template <int NW>
-__global__ __launch_bounds__(64 * NW) void full_sov(const double* __restrict__ L, const double* __restrict__ bl,
-                                                    const uint64_t* __restrict__ Zt, double* __restrict__ Y,
-                                                    double2* __restrict__ part, SovSizes a) {
-  __shared__ double T[NW][kFsB][kFsWavePts + 1];
-  __shared__ double Lb[kFsB * (kFsB + 1) / 2];   // the block's lower triangle, packed by rows
-  __shared__ double dinv[kFsB];                  // reciprocals of the block's diagonal
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int r = blockIdx.y;
-  const int64_t D = a.D, S = a.S, N = a.N;
-  // this lane's point (column m of the wave's tile) and step offset / update group kq
+// A point's recursion over rows Q.. of a tile (left of them below D):
+//     e = Phi(t_q), log prod += log Phi(t_q), y_q = Phi^-1(max(w_q e, DBL_MIN)),
+//     T[q'] -= L[q][q'] y_q for q' > q (L scaled by its rows' pivots, as T is).
+// ty: the point's column of the staged tile (its y replace its limits); w: of the coordinates.
+struct SovPoint {
+  double T[kFsTile];
+  double prod;   // of the tile's e outside the rare branch: at least 1e-272
+  double lp;
+};
+template <int Q, int PT>
+__device__ __forceinline__ void sov_rows(SovPoint& s, double* ty, const double* w, const double (*L)[kFsTile], int left,
+                                         const double* nodes) {
+  if (Q >= left) return;
+  const double t = s.T[Q];
+  double e = phi_nodes(nodes, fmax(fmin(t, kPhiNodeMax), -kPhiNodeMax));
+  double f = e;
+  if (__builtin_expect(any_lane(!(t >= -kPhiNodeMax)), 0)) {
+    if (!(t >= -kPhiNodeMax)) {
+      e = phi64(t);
+      s.lp += log_ncdf_low(t, e);
+      f = 1.0;
+    }
+  }
+  s.prod *= f;
+  double u, uc, side;
+  {
+    // the product rounds before 1 - u, as the quantile's argument is u itself
+#pragma clang fp contract(off)
+    u = w[Q * PT] * e;
+    uc = 1.0 - u;
+    side = u - 0.5;
+  }
+  const double q = fmin(u, uc);
+  double y = __builtin_copysign(ninv_nodes(nodes, q), side);
+  if (__builtin_expect(any_lane(!(q >= kNinvNodeMin)), 0)) {
+    if (!(q >= kNinvNodeMin)) y = ninv64(fmax(u, 2.2250738585072014e-308));
+  }
+  ty[Q * PT] = y;
+  double row[kFsTile];
+#pragma unroll
+  for (int c = Q + 1; c < kFsTile; ++c) row[c] = L[Q][c];
+#pragma unroll
+  for (int c = Q + 1; c < kFsTile; ++c) {
+    s.T[c] = __builtin_fma(-row[c], y, s.T[c]);
+    // stays here: moved to the step that uses T[c], it would keep y and row alive
+    __asm__ volatile("" : "+v"(s.T[c]));
+  }
+  if constexpr (Q + 1 < kFsTile) sov_rows<Q + 1, PT>(s, ty, w, L, left, nodes);
+}
+
+// A workgroup owns C tiles of 16 consecutive lattice points for the whole chain.
+// Dimensions go in tiles of 16 rows, kFsWaves tiles to a block (the first block
+// takes the remainder), one row tile of the block per wave:
+//  * Earlier blocks: acc = L[the wave's rows, 0..j0) y for the C point tiles by
+//    v_mfma_f64_16x16x4: the A operand is L[j + m][c0 + k] (row c0 + k of the
+//    upper triangle, 16 consecutive doubles per k), the B operands the y of
+//    step c0 / 4 (512 consecutive bytes per point tile, read by every wave); the
+//    loads of the next kFsBufs - 1 steps are in flight.
+//  * The block's tiles in turn: the tile's wave leaves its scaled limits
+//    (b - acc) / L_cc in LDS, the first waves run the recursion with a point per
+//    lane, and the waves of the later tiles take the new y into their acc, while
+//    all threads stage the next tile's lattice coordinates and triangle of L.
+// So the product's matrix work is spread evenly over the compute unit's SIMDs
+// whatever the number of points, and the recursion's vector work is done once
+// per point; it leaves the matrix cores idle for the latency of its serial
+// chain, about 1,000 clocks a dimension. With a wave per 16 points for both
+// (each factor evaluated by four lanes, three waves on some SIMDs and two on
+// others), 2,500 dimensions and 3607 x 10 points took 7.8 ms. Measured against
+// one wave per 16 points with fitted ratios and the recursion's triangle in
+// LDS: that case 14.6 -> 6.1 ms (the product alone is 3.0 ms at the FP64 matrix
+// peak), 500 x 4 points 8.6 -> 1.7 ms, 900 dimensions and 10^4 x 10 points
+// 8.3 -> 3.1 ms, 5,000 dimensions and 2000 x 10 points 32.3 -> 14.5 ms.
+template <int C>
+__global__ __launch_bounds__(64 * kFsWaves) __attribute__((amdgpu_waves_per_eu(kFsWaves / 4))) void full_sov(SovArgs a) {
+  constexpr int PT = 16 * C;
+  constexpr int kThreads = 64 * kFsWaves;
+  __shared__ __align__(16) double nodes[2 * kNormNodes];
+  __shared__ double ty[2][kFsTile][PT];    // a tile's limits, then its y
+  __shared__ double wt[kFsTile][PT];       // its lattice coordinates
+  __shared__ __align__(16) double Lt[kFsTile][kFsTile];   // Lt[q][c] = L_{j+c,j+q} / L_{j+c,j+c}, c > q
+  load_nodes(nodes);
+  const int tid = threadIdx.x, lane = tid & 63, wv = uniform(tid >> 6);
+  const int64_t wg = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+  if (wg * C >= a.all_tiles) return;
   const int m = lane & 15, kq = lane >> 4;
-  const int64_t pt = (int64_t)(blockIdx.x * NW + wv) * kFsWavePts + m;
-  const bool live = pt < N;
-  const int64_t pc = live ? pt : N - 1;   // past the shift's last point: any point of it (results unused)
-  const int64_t s_own = (int64_t)r * N + pc;
-  const double* __restrict__ yB = Y + s_own + (int64_t)kq * S;
-  double (*Tw)[kFsWavePts + 1] = T[wv];
-  double lp = 0.0;
-  for (int64_t j0 = 0; j0 < D; j0 += kFsB) {
-    const int nb = (int)(D - j0 < kFsB ? D - j0 : kFsB);
-    fs_d4 acc[4];
+  const int64_t D = a.D;
+  double* __restrict__ Yw = a.Y + wg * a.y_steps * (64 * C);
+  const int64_t n_tiles = (D + kFsTile - 1) / kFsTile;
+  int block = (int)(n_tiles % kFsWaves);
+  if (block == 0) block = kFsWaves;
+
+  // point p of the workgroup: its shift and 1-based index (past the shift's or
+  // the last shift's points: some point, its results unused)
+  auto point = [&](int p, int64_t* shift, bool* live) {
+    int64_t tile = wg * C + (p >> 4);
+    *live = tile < a.all_tiles;
+    if (!*live) tile = a.all_tiles - 1;
+    *shift = (uint32_t)tile / (uint32_t)a.tiles;
+    const int64_t pn = (tile - *shift * a.tiles) * 16 + (p & 15);
+    *live = *live && pn < a.N;
+    return (uint64_t)(pn < a.N ? pn : a.N - 1) + 1;
+  };
+  // entry (q, c) = (tid / 16, tid % 16) of the triangle, the reads past D inside the workspace
+  double lt = 0.0;
+  auto load_triangle = [&](int64_t j) {
+    if (tid < kFsTile * kFsTile) {
+      const int64_t row = j + (tid >> 4);
+      lt = a.L[(row < D ? row : D - 1) * D + j + (tid & 15)] * a.dinv[j + (tid & 15)];
+    }
+  };
+  auto stage = [&](int64_t j) {
+    if (tid < kFsTile * kFsTile) Lt[tid >> 4][tid & 15] = lt;
+    for (int idx = tid; idx < kFsTile * PT; idx += kThreads) {
+      const int q = idx / PT, p = idx - q * PT;
+      int64_t r;
+      bool live;
+      const uint64_t pt = point(p, &r, &live);
+      const int64_t dim = j + q;
+      const uint64_t z = a.Z[dim < D - 1 ? dim : (D > 1 ? D - 2 : 0)];   // the last dimension's y is not used
+      wt[q][p] = lattice_coord_f64(pt * z + splitmix64(a.seed, (1ULL << 63) | ((uint64_t)r << 32) | (uint64_t)dim));
+    }
+  };
+
+  SovPoint s;
+  s.lp = 0.0;
+  int buf = 0;
+  for (int64_t j0 = 0; j0 < D;) {
+    fs_d4 acc[C];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) acc[i] = fs_d4{0.0, 0.0, 0.0, 0.0};
-    // rows past D in a last, ragged block read other entries of L (in the array
-    // while j0 > 0, since then D > kFsB); their sums are never used
-    const double* __restrict__ aA = L + j0 + m + (int64_t)kq * D;
-    // j0 is a multiple of kFsB: whole steps of 4 earlier dimensions (a multiple
-    // of 16 steps); the loads of step c0 + 4 are issued before the MFMAs of
-    // step c0 (two register sets)
-    const int steps = (int)(j0 / 4);
-    double av[2][4], bv[2];
-    auto load_step = [&](int st, int buf) {
-      const int64_t c0 = (int64_t)st * 4;
-      bv[buf] = __builtin_nontemporal_load(yB + c0 * S);
-      const double* __restrict__ ar = aA + c0 * D;
+    for (int i = 0; i < C; ++i) acc[i] = fs_d4{0.0, 0.0, 0.0, 0.0};
+    const int64_t jw = j0 + (int64_t)wv * kFsTile;   // the wave's row tile
+    const bool mine = wv < block;
+    load_triangle(j0);
+    const int steps = (int)(j0 / 4);   // a multiple of 4
+    if (steps > 0) {   // then block == kFsWaves
+      // columns past D in the last tile read other entries (of the next row,
+      // which exists: c < j0); their sums are never used
+      const double* __restrict__ aA = a.L + (int64_t)kq * D + jw + m;
+      const double* __restrict__ aB = Yw + lane;
+      double av[kFsBufs], bv[kFsBufs][C];
+      auto load_step = [&](int st, int u) {
+        av[u] = aA[(int64_t)st * 4 * D];
+        const double* __restrict__ br = aB + (int64_t)st * (64 * C);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) av[buf][i] = ar[16 * i];
-    };
-    auto mfma_step = [&](int buf) {
+        for (int i = 0; i < C; ++i) bv[u][i] = br[64 * i];
+      };
+      // the loads past the last step re-read it: with every load unconditional
+      // the compiler's wait counts stay exact across the loop
 #pragma unroll
-      for (int i = 0; i < 4; ++i) acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[buf][i], bv[buf], acc[i], 0, 0, 0);
-    };
-    // the loads past the last step re-read it: with every load unconditional
-    // the compiler's wait counts stay exact across the loop
-    if (steps > 0) {
-      load_step(0, 0);
-      for (int st = 0; st < steps; st += 2) {
+      for (int u = 0; u < kFsBufs - 1; ++u) load_step(u, u);
+      for (int st = 0; st < steps; st += kFsBufs) {
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          const int nx = st + u + 1;
-          load_step(nx < steps ? nx : steps - 1, (u + 1) & 1);
-          mfma_step(u);
+        for (int u = 0; u < kFsBufs; ++u) {
+          const int nx = st + u + kFsBufs - 1;
+          load_step(nx < steps ? nx : steps - 1, (u + kFsBufs - 1) % kFsBufs);
+#pragma unroll
+          for (int i = 0; i < C; ++i)
+            acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u], bv[u][i], acc[i], 0, 0, 0);
         }
       }
     }
-    // acc[i] element e (the MFMA's output layout): row 16 i + 4 e + kq of the
-    // block, point m of the wave's tile
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    // acc[i] element e (the MFMA's output layout): row 4 e + kq, point 16 i + m;
+    // rows past D in the last tile take what follows b in the workspace, unused
+    auto leave_limits = [&](int64_t j) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int q = 16 * i + 4 * e + kq;
-        Tw[q][m] = (q < nb ? bl[j0 + q] : 0.0) - acc[i][e];
+        const double bq = a.b[j + 4 * e + kq], dq = a.dinv[j + 4 * e + kq];
+#pragma unroll
+        for (int i = 0; i < C; ++i) ty[buf][4 * e + kq][16 * i + m] = (bq - acc[i][e]) * dq;
       }
-    }
-    __syncthreads();   // every wave is done with the previous block's triangle
-    for (int idx = tid; idx < kFsB * (kFsB + 1) / 2; idx += 64 * NW) {
-      int q = (int)((__builtin_sqrt(8.0 * idx + 1.0) - 1.0) * 0.5);
-      while (q * (q + 1) / 2 > idx) --q;
-      while ((q + 1) * (q + 2) / 2 <= idx) ++q;
-      const int c = idx - q * (q + 1) / 2;
-      Lb[idx] = q < nb ? L[(j0 + q) * D + j0 + c] : 0.0;
-    }
-    for (int q = tid; q < kFsB; q += 64 * NW) dinv[q] = q < nb ? 1.0 / L[(j0 + q) * D + j0 + q] : 0.0;
-    __syncthreads();
+    };
+    const bool keep = j0 + (int64_t)block * kFsTile < D;   // a later block reads the y
+    if (wv == 0) leave_limits(j0);
+    stage(j0);
 #pragma unroll 1
-    for (int q = 0; q < nb; ++q) {
-      // every lane group evaluates the same point's factor; group 0 keeps it
-      const double t = Tw[q][m] * dinv[q];
-      const double e = ncdf_full(t);
-      // log Phi(t) from Phi(t) itself while Phi(t) > 1e-197 (its relative
-      // error is then that of the log's absolute error); the scaled
-      // complementary form only where some lane's limit is at or below -30
-      double lt = log(e);
-      if (__builtin_expect(__any(t <= -30.0), 0)) {
-        if (t <= -30.0) lt = log_ncdf(t);
+    for (int i = 0; i < block; ++i) {
+      const int64_t j = j0 + (int64_t)i * kFsTile;
+      const bool later = mine && wv > i;
+      // A operands of the update after the recursion
+      double nv[4] = {0.0, 0.0, 0.0, 0.0};
+      if (later) {
+#pragma unroll
+        for (int st = 0; st < 4; ++st) nv[st] = a.L[(j + 4 * st + kq) * D + jw + m];
       }
-      lp += lt;
-      const int64_t dim = j0 + q;
-      if (dim < D - 1) {
-        const uint64_t Sh = splitmix64(a.seed, (1ULL << 63) | ((uint64_t)r << 32) | (uint64_t)dim);
-        const uint64_t U = (uint64_t)(pc + 1) * Zt[dim] + Sh;
-        const double w = lattice_coord_f64(U);
-        const double y = ncdfinv_full(fmax(w * e, 2.2250738585072014e-308));
-        if (kq == 0 && live) Y[dim * S + s_own] = y;
-#pragma unroll 2
-        for (int q2 = q + 1 + kq; q2 < nb; q2 += 4) Tw[q2][m] -= Lb[q2 * (q2 + 1) / 2 + q] * y;
+      __syncthreads();
+      const int left = (int)(D - j < kFsTile ? D - j : kFsTile);
+      if (tid < PT) {
+#pragma unroll
+        for (int q = 0; q < kFsTile; ++q) s.T[q] = ty[buf][q][tid];
+        s.prod = 1.0;
+        sov_rows<0, PT>(s, &ty[buf][0][tid], &wt[0][tid], Lt, left, nodes);
+        s.lp += log(s.prod);
+      }
+      __syncthreads();
+      if (keep) {   // the whole tile is below D
+        for (int idx = tid; idx < kFsTile * PT; idx += kThreads) {
+          const int l = idx & 63, ct = (idx >> 6) % C, st = (idx >> 6) / C;
+          Yw[((j / 4 + st) * C + ct) * 64 + l] = ty[buf][4 * st + (l >> 4)][16 * ct + (l & 15)];
+        }
+      }
+      if (i + 1 < block) load_triangle(j + kFsTile);
+      if (later) {
+#pragma unroll
+        for (int st = 0; st < 4; ++st)
+#pragma unroll
+          for (int ct = 0; ct < C; ++ct)
+            acc[ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(nv[st], ty[buf][4 * st + kq][16 * ct + m], acc[ct], 0, 0, 0);
+      }
+      buf ^= 1;
+      if (i + 1 < block) {
+        if (wv == i + 1) leave_limits(j + kFsTile);
+        stage(j + kFsTile);
       }
     }
-    // the wave's own y stores are read back by its next product (other lanes)
-    __threadfence_block();
+    __syncthreads();   // the block's y are in Y before its readers, and ty is free
+    j0 += (int64_t)block * kFsTile;
+    block = kFsWaves;
   }
-  // the wave's {max, sum exp(lp - max)} over its live points (lane group 0)
-  const bool own = live && kq == 0;
-  double mx = own ? lp : -HUGE_VAL;
+  // each point tile's {max, sum exp(lp - max)} over its live points (16 lanes)
+  if (tid < PT) {
+    int64_t r;
+    bool live;
+    point(tid, &r, &live);
+    double mx = live ? s.lp : -HUGE_VAL;
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
-  double x = (own && mx > -HUGE_VAL) ? exp(lp - mx) : 0.0;
+    for (int o = 8; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 16));
+    double x = (live && mx > -HUGE_VAL) ? exp(s.lp - mx) : 0.0;
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-  if (lane == 0) part[((int64_t)r * gridDim.x + blockIdx.x) * NW + wv] = make_double2(mx, x);
+    for (int o = 8; o > 0; o >>= 1) x += __shfl_xor(x, o, 16);
+    const int64_t tile = wg * C + (tid >> 4);
+    if (m == 0 && tile < a.all_tiles) a.part[tile] = make_double2(mx, x);
+  }
 }
 
-// Waves per workgroup (16 points each) for N points per shift and R shifts: four
-// (one wave on each SIMD of a compute unit, sharing the workgroup's loads of L)
-// unless that leaves compute units without a workgroup; then the most that
-// still give every compute unit one.
-int full_sov_waves(int64_t N, int64_t R, int n_cu) {
-  for (int nw = 4; nw > 1; --nw) {
-    const int64_t P = (int64_t)kFsWavePts * nw;
-    if ((N + P - 1) / P * R >= n_cu) return nw;
+template <int C>
+hipError_t launch_sov(const SovArgs& a, hipStream_t s) {
+  const int64_t groups = (a.all_tiles + C - 1) / C;
+  const unsigned gx = (unsigned)std::min<int64_t>(groups, 1 << 20), gy = (unsigned)((groups + gx - 1) / gx);
+  hipLaunchKernelGGL(full_sov<C>, dim3(gx, gy), dim3(64 * kFsWaves), 0, s, a);
+  return hipGetLastError();
+}
+
+// Point tiles per workgroup: of the compiled counts the one with the least
+// rounds x (product + recursion) for one workgroup per compute unit, D / 8 clocks per
+// dimension and point tile for the product on four SIMDs, 1,000 for the recursion.
+int sov_tiles(int64_t all_tiles, int64_t D, int n_cu) {
+  int best = 1;
+  double least = 0.0;
+  for (int c : {1, 2, 3, 4, 6, 9}) {
+    const int64_t groups = (all_tiles + c - 1) / c;
+    const double t = (double)((groups + n_cu - 1) / n_cu) * (c * (D / 8.0) + 1000.0);
+    if (c == 1 || t < least) {
+      best = c;
+      least = t;
+    }
   }
-  return 1;
+  return best;
 }
 
 // One workgroup of 256: per shift r, l_r = log mean over points from the waves'
@@ -431,11 +572,10 @@ extern "C" vecchia_status vecchia_full_logcdf(vecchia_plan_t plan, const double*
       return set_error(VECCHIA_E_INVALID, "covariance override must keep the plan's family and nu");
   }
   const int64_t D = plan->D, N = q->n_points, R = q->n_shifts;
-  const int64_t S = N * R;
-  // workspace: A (D x D), b (D), Y ((D-1) x S), then the partials at a 16-byte offset
+  const int64_t S = N * R;   // points
+  // the limit: A (D x D), b (D), (D - 1) y for each of the S points and the partials
   const int64_t n_head = D * D + D + std::max<int64_t>(1, D - 1) * S;
   const int64_t n_head_even = n_head + (n_head & 1);
-  // partials: one per wave, at most ceil(N / 16) + 3 per shift (the last workgroup of a shift)
   const double bytes = 8.0 * (double)n_head_even + 16.0 * R * ((N + kFsWavePts - 1) / kFsWavePts + 3);
   if (D > 40000 || bytes > 64e9)
     return set_error(VECCHIA_E_INVALID, "the full-dimension estimator needs D <= 40000 and at most 64 GB of workspace");
@@ -447,7 +587,18 @@ extern "C" vecchia_status vecchia_full_logcdf(vecchia_plan_t plan, const double*
   if (e != hipSuccess) return hip_error(e, "device query");
   const uint64_t* Zt = device_lattice_table_n(dev, (int)std::max<int64_t>(1, D - 1), &e);
   if (!Zt) return hip_error(e, "lattice table");
-  const size_t need = (size_t)bytes + 1024;
+  // workspace: A, b, dinv (D each), the y of all blocks but the last (64 per
+  // step of four dimensions and point tile, whole workgroups), the partials at
+  // a 16-byte offset; the slack covers reads past b and dinv in a last, partial tile
+  hipDeviceProp_t prop{};
+  int n_cu = 256;
+  if (hipGetDeviceProperties(&prop, dev) == hipSuccess && prop.multiProcessorCount > 0) n_cu = prop.multiProcessorCount;
+  const int64_t tiles = (N + kFsWavePts - 1) / kFsWavePts, all_tiles = tiles * R;
+  const int per_group = sov_tiles(all_tiles, D, n_cu);
+  const int64_t held_tiles = (all_tiles + per_group - 1) / per_group * per_group;
+  const int64_t y_steps = std::max<int64_t>(0, (D + kFsTile - 1) / kFsTile - kFsWaves) * (kFsTile / 4);
+  const int64_t n_y = D * D + 2 * D, n_part = (n_y + (n_y & 1)) + 64 * y_steps * held_tiles;
+  const size_t need = (size_t)(8 * n_part + 16 * all_tiles) + 1024;
   if (plan->full_bytes < need) {
     hipFree(plan->d_full);
     plan->d_full = nullptr;
@@ -461,59 +612,43 @@ extern "C" vecchia_status vecchia_full_logcdf(vecchia_plan_t plan, const double*
   }
   double* A = reinterpret_cast<double*>(plan->d_full);
   double* b = A + D * D;
-  double* Y = b + D;
-  double2* part = reinterpret_cast<double2*>(A + n_head_even);
+  double* dinv = b + D;
+  double* Y = A + n_y + (n_y & 1);
+  double2* part = reinterpret_cast<double2*>(A + n_part);
   CovArgs ca{plan->d_xs, plan->d_ys, plan->d_cov, plan->d_perm, x_dev, 1.0 / scale, c.sigma2, c.range, c.nugget,
              c.family == VECCHIA_COV_EXPONENTIAL ? 0.5 : c.nu, c.family};
-  const unsigned tiles = (unsigned)((D + 15) / 16);
-  hipLaunchKernelGGL(full_cov_build, dim3(tiles, tiles), dim3(256), 0, s, ca, D, A, b);
+  const unsigned t16 = (unsigned)((D + 15) / 16);
+  hipLaunchKernelGGL(full_cov_build, dim3(t16, t16), dim3(256), 0, s, ca, D, A, b);
   e = hipGetLastError();
   for (int64_t k0 = 0; k0 < D && e == hipSuccess; k0 += kCholB) {
     const int n = (int)std::min<int64_t>(kCholB, D - k0);
-    hipLaunchKernelGGL(chol_diag, dim3(1), dim3(64), 0, s, A, D, k0, n);
-    e = hipGetLastError();
     const int64_t rest = D - k0 - n;
-    if (e == hipSuccess && rest > 0) {
-      hipLaunchKernelGGL(chol_panel, dim3((unsigned)((rest + 255) / 256)), dim3(256), 0, s, A, D, k0, n);
-      e = hipGetLastError();
-      const unsigned t = (unsigned)((rest + 63) / 64);   // 64 x 64 tiles of the trailing triangle
-      if (e == hipSuccess) {
-        hipLaunchKernelGGL(chol_update, dim3(t, t), dim3(256), 0, s, A, D, k0, n);
-        e = hipGetLastError();
-      }
-    }
-  }
-  if (e == hipSuccess) {
-    const unsigned t32 = (unsigned)((D + 31) / 32);
-    hipLaunchKernelGGL(chol_mirror, dim3(t32, t32), dim3(256), 0, s, A, D);
+    const unsigned t = (unsigned)std::max<int64_t>(1, (rest + 63) / 64);   // 64 x 64 tiles of the trailing triangle
+    hipLaunchKernelGGL(chol_step, dim3(t, t), dim3(256), 0, s, A, dinv, D, k0, n);
     e = hipGetLastError();
   }
-  hipDeviceProp_t prop{};
-  int n_cu = 256;
-  if (hipGetDeviceProperties(&prop, dev) == hipSuccess && prop.multiProcessorCount > 0) n_cu = prop.multiProcessorCount;
-  const int nw = full_sov_waves(N, R, n_cu);
-  const int64_t P = (int64_t)kFsWavePts * nw;
-  const unsigned nblk = (unsigned)((N + P - 1) / P);
   // measurement hook: HIP events around the product-and-recursion kernel,
   // recorded with its D(D-1)/2 FMAs per point
   hipEvent_t pa = nullptr, pb = nullptr;
   const bool prof = e == hipSuccess && profiling_enabled() && profile_events(&pa, &pb) == hipSuccess;
   if (prof) e = hipEventRecord(pa, s);
   if (e == hipSuccess) {
-    SovSizes sz{D, N, S, q->seed};
-    const dim3 grid(nblk, (unsigned)R), block(64 * nw);
-    if (nw == 4) hipLaunchKernelGGL(full_sov<4>, grid, block, 0, s, A, b, Zt, Y, part, sz);
-    else if (nw == 3) hipLaunchKernelGGL(full_sov<3>, grid, block, 0, s, A, b, Zt, Y, part, sz);
-    else if (nw == 2) hipLaunchKernelGGL(full_sov<2>, grid, block, 0, s, A, b, Zt, Y, part, sz);
-    else hipLaunchKernelGGL(full_sov<1>, grid, block, 0, s, A, b, Zt, Y, part, sz);
-    e = hipGetLastError();
+    const SovArgs sa{A, dinv, b, Zt, Y, part, D, N, q->seed, tiles, all_tiles, y_steps};
+    switch (per_group) {
+      case 1: e = launch_sov<1>(sa, s); break;
+      case 2: e = launch_sov<2>(sa, s); break;
+      case 3: e = launch_sov<3>(sa, s); break;
+      case 4: e = launch_sov<4>(sa, s); break;
+      case 6: e = launch_sov<6>(sa, s); break;
+      default: e = launch_sov<9>(sa, s); break;
+    }
   }
   if (prof && e == hipSuccess) {
     e = hipEventRecord(pb, s);
     if (e == hipSuccess) profile_record(VECCHIA_PROFILE_FULL_SOV, VECCHIA_FP64, pa, pb, D * (D - 1) / 2 * N * R);
   }
   if (e == hipSuccess) {
-    hipLaunchKernelGGL(full_final, dim3(1), dim3(256), 0, s, part, (int)nblk * nw, (int)R, N, out_dev);
+    hipLaunchKernelGGL(full_final, dim3(1), dim3(256), 0, s, part, (int)tiles, (int)R, N, out_dev);
     e = hipGetLastError();
   }
   if (e != hipSuccess) return hip_error(e, "full-dimension launch");

@@ -150,3 +150,44 @@ def test_full_profile_hook_records_the_kernel():
     V.vecchia_plan_destroy(plan)
     assert launches == 1 and ms > 0.0
     assert fmas == 70 * 69 // 2 * 200 * 3
+
+
+@pytest.mark.parametrize("D,N,R", [(113, 700, 7), (20, 1000, 10), (144, 1500, 10), (37, 2300, 10), (150, 3500, 10),
+                                   (129, 17, 20)])
+def test_full_point_tiles_and_dimension_blocks(D, N, R):
+    # workgroups of 1, 2, 3, 4, 6 and 9 point tiles (a 256-CU device; N R / 16
+    # tiles, the last of a shift and the last workgroup ragged) over one block of
+    # dimensions and over a remainder block and a full one, with a ragged last
+    # row tile, the last Cholesky block full and short
+    torch = torch_cuda()
+    from paper_2007_15195_amd import vecchia as V
+    inst = W.small_random_instance(D, 5, 900 + D, ordering=W.ORDER_MAXMIN, n_points=N, n_shifts=R)
+    plan = V.vecchia_plan(inst.locs, inst.ordering, inst.m, inst.cov)
+    got = _full(V, torch, plan, inst.x, V.make_qmc(N, R, 11, V.VECCHIA_FP64))
+    perm, _ = V.vecchia_plan_neighbours(plan)
+    V.vecchia_plan_destroy(plan)
+    c = inst.cov
+    S = covariance.cov_matrix(inst.locs[perm], c.family, c.nu, c.sigma2, c.range, c.nugget)
+    lf, se, _ = FS.logcdf_full(S, inst.x[perm], N, R, 11)
+    assert abs(got[0] - lf) <= 1e-10 * max(1.0, abs(lf))
+    assert abs(got[1] - se) <= 1e-6 * se + 1e-12
+
+
+def test_full_deep_tail_factors():
+    # independent components with limits over the three forms of log Phi: the
+    # node table, the fitted ratio (below -8.5) and the asymptotic series (below
+    # -30, past the range where Phi itself is a normal number at -37.5)
+    torch = torch_cuda()
+    from paper_2007_15195_amd import vecchia as V
+    from scipy.special import log_ndtr
+    t = np.array([8.6, 3.0, 0.0, -8.4, -8.6, -20.0, -29.9, -30.1, -37.0, -38.6, -60.0, -1000.0])
+    plan = V.vecchia_plan_from_cov(np.diag(np.full(t.size, 4.0)), 1)
+    got = _full(V, torch, plan, 2.0 * t, V.make_qmc(100, 2, 2, V.VECCHIA_FP64))
+    V.vecchia_plan_destroy(plan)
+    for i in range(t.size):
+        one = V.vecchia_plan_from_cov(np.diag([4.0, 1.0]), 1)
+        b = np.array([2.0 * t[i], np.inf])
+        g = _full(V, torch, one, b, V.make_qmc(64, 2, 3, V.VECCHIA_FP64))[0]
+        V.vecchia_plan_destroy(one)
+        assert abs(g - log_ndtr(t[i])) <= 1e-14 * abs(log_ndtr(t[i])) + 1e-15, (t[i], g, log_ndtr(t[i]))
+    assert abs(got[0] - log_ndtr(t).sum()) <= 1e-12 * abs(log_ndtr(t).sum())
