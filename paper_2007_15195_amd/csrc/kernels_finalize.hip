@@ -13,8 +13,9 @@
 // With independent points (passes = 2) the denominators come from the second
 // lattice's sums and se^2 = R/(R-1) sum_r [(num_r / sum num - 1/R)^2 + (den_r / sum den - 1/R)^2].
 // Results go to a per-term array and, when asked for, to the user-order output.
-// In an FP32 evaluation a term whose SE exceeds kRedoSe is not written by this
-// pass: it goes to the re-run list, whose FP64 pass term_finalize_redo finalizes.
+// In an FP32 evaluation a term promoted at set-up is left to term_finalize_redo,
+// and so is a term whose SE exceeds kRedoSe, which goes to the re-run list: both
+// lists share one FP64 pass between the two finalizes.
 //
 // instance_logsum: one block per instance sums its terms' log-terms and se^2 in
 // a fixed order (per-thread strided partial sums, then a fixed tree), so the
@@ -51,6 +52,7 @@ __device__ __forceinline__ void finalize_term(const InstDesc* __restrict__ insts
   const int lane = threadIdx.x & 63;
   const int ii = find_inst(term_bases, n_inst, t);
   const InstDesc& I = insts[ii];
+  if (allow_redo && I.precision == VECCHIA_FP32_LOOP && I.promote[t] != 0) return;   // its FP64 pass comes after this one
   const int64_t i = t - term_bases[ii];
   const int R = I.n_shifts;
   double lt, se2;
@@ -132,15 +134,16 @@ __global__ __launch_bounds__(64 * kFinalizeWaves) void term_finalize(
   finalize_term(insts, n_inst, term_bases, aux64, sums, term_res, t, allow_redo != 0);
 }
 
-// The re-run list's terms after their FP64 pass, one per wave in turn.
+// Both lists' terms after their FP64 pass, one per wave in turn.
 __global__ __launch_bounds__(64 * kFinalizeWaves) void term_finalize_redo(
     const InstDesc* __restrict__ insts, int n_inst, const int64_t* __restrict__ term_bases,
     const Aux64* __restrict__ aux64, const double* __restrict__ sums, double2* __restrict__ term_res,
-    const int32_t* __restrict__ list, const int64_t* __restrict__ count, int64_t cap) {
-  const int64_t n = min(*count, cap);
+    const int32_t* __restrict__ list, const int64_t* __restrict__ ctr, int64_t cap) {
+  const int64_t first = min(ctr[0], cap), n = first + min(ctr[2], cap);
   const int64_t waves = (int64_t)gridDim.x * kFinalizeWaves;
   for (int64_t e = (int64_t)blockIdx.x * kFinalizeWaves + (threadIdx.x >> 6); e < n; e += waves)
-    finalize_term(insts, n_inst, term_bases, aux64, sums, term_res, (int64_t)list[e], false);
+    finalize_term(insts, n_inst, term_bases, aux64, sums, term_res, (int64_t)list[e < first ? e : cap + (e - first)],
+                  false);
 }
 
 __global__ __launch_bounds__(kFinalizeThreads) void instance_logsum(const InstDesc* __restrict__ insts,
@@ -288,11 +291,11 @@ hipError_t launch_finalize_terms(const InstDesc* d_insts, int n_inst, const int6
 
 hipError_t launch_finalize_redo(const InstDesc* d_insts, int n_inst, const int64_t* d_term_bases,
                                 const Aux64* aux64, const double* sums, double2* term_res,
-                                const int32_t* list, const int64_t* count, int64_t cap, hipStream_t s) {
+                                const int32_t* list, const int64_t* ctr, int64_t cap, hipStream_t s) {
   if (n_inst <= 0 || cap <= 0) return hipSuccess;
   const int64_t blocks = (cap + kFinalizeWaves - 1) / kFinalizeWaves;
   hipLaunchKernelGGL(term_finalize_redo, dim3((unsigned)(blocks < 256 ? blocks : 256)), dim3(64 * kFinalizeWaves), 0,
-                     s, d_insts, n_inst, d_term_bases, aux64, sums, term_res, list, count, cap);
+                     s, d_insts, n_inst, d_term_bases, aux64, sums, term_res, list, ctr, cap);
   return hipGetLastError();
 }
 

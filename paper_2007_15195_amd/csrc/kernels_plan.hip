@@ -240,9 +240,10 @@ __global__ __launch_bounds__(256) void knn_grid(const double* __restrict__ xs, c
     if (s < m) nbr[i * m + s] = s < k ? bj[s] : -1;
 }
 
-__global__ void fill_i64(int64_t* p, int64_t n, int64_t v) {
+__global__ void init_call(int64_t* bad, int64_t n, int64_t* pctr) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = v;
+  if (i < n) bad[i] = INT64_MAX;
+  if (pctr && i < 3) pctr[i] = 0;
 }
 
 __global__ void fill_i32(int32_t* p, int64_t n, int32_t v) {
@@ -309,9 +310,9 @@ hipError_t build_grid(const double* xs, const double* ys, int64_t D, const KnnGr
 
 }  // namespace
 
-hipError_t launch_fill_i64(int64_t* p, int64_t n, int64_t v, hipStream_t s) {
+hipError_t launch_init_call(int64_t* bad, int64_t n, int64_t* pctr, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(fill_i64, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p, n, v);
+  hipLaunchKernelGGL(init_call, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, bad, n, pctr);
   return hipGetLastError();
 }
 

@@ -203,9 +203,9 @@ __device__ __forceinline__ int find_inst_q(const int64_t* __restrict__ bases, in
   return lo;
 }
 
-// Handed-over terms of FP32 instances: each wave takes the next (list entry,
-// item) pair from the work counter ctr[1] until the count x ipt_max pairs are
-// used up; pairs past a term's own item count are skipped. Every wave leaves
+// Handed-over terms of FP32 instances, from both lists: each wave takes the next
+// (list entry, item) pair from the work counter ctr[1] until the counts x ipt_max
+// pairs are used up; pairs past a term's own item count are skipped. Every wave leaves
 // once the counter passes the end, so the grid always drains. K covers every
 // term of the batch's FP32 instances.
 template <int K>
@@ -216,8 +216,8 @@ __global__ __launch_bounds__(64 * f64_waves(K)) __attribute__((amdgpu_waves_per_
   constexpr int W = f64_waves(K);
   __shared__ __align__(16) double nodes[2 * kNormNodes];
   __shared__ uint64_t sh[K > kF64AdvanceK ? W * K : 1];
-  const int64_t count = min(ctr[0], cap);
-  const int64_t total = count * (int64_t)ipt_max;
+  const int64_t first = min(ctr[0], cap);
+  const int64_t total = (first + min(ctr[2], cap)) * (int64_t)ipt_max;
   if ((int64_t)blockIdx.x * W >= total) return;   // fewer pairs than waves: no tables, no work counter
   load_nodes(nodes);
   const int lane = threadIdx.x & 63, wv = uniform(threadIdx.x >> 6);
@@ -238,7 +238,7 @@ __global__ __launch_bounds__(64 * f64_waves(K)) __attribute__((amdgpu_waves_per_
     if (v >= total) break;
     const int64_t e = v / ipt_max;
     const int j = (int)(v - e * ipt_max);
-    const int64_t t = uniform(list[e]);
+    const int64_t t = uniform(list[e < first ? e : cap + (e - first)]);
     const int ii = uniform(find_inst_q(term_bases, n_inst, t));
     const InstDesc& I = insts[ii];
     const int ns = uniform(I.n_shifts), nc = uniform(I.n_chunks);

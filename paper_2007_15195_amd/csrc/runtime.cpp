@@ -403,7 +403,7 @@ vecchia_status Batch::create(const std::vector<vecchia_plan_s*>& plans,
     b->plist_cap_ = (int32_t)tb;
     take(sizeof(int32_t) * tb);
     take(sizeof(int32_t) * 2 * (size_t)tb);
-    take(sizeof(int64_t) * 4);
+    take(sizeof(int64_t) * 3);
   }
   b->ws_bytes_ = off;
   *out = std::move(b);
@@ -430,7 +430,7 @@ void Batch::carve(char* base) {
   if (any_f32_) {
     d_promote_ = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * total_terms_));
     d_plist_ = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * 2 * (size_t)total_terms_));
-    d_pctr_ = reinterpret_cast<int64_t*>(take(sizeof(int64_t) * 4));
+    d_pctr_ = reinterpret_cast<int64_t*>(take(sizeof(int64_t) * 3));
   }
   ipt_max_ = 0;
   for (int j = 0; j < n; ++j) {
@@ -491,8 +491,7 @@ vecchia_status Batch::allocate() {
 vecchia_status Batch::enqueue(hipStream_t s, bool allow_profile) {
   const int n = (int)plans_.size();
   const bool prof = allow_profile && profiling_enabled();
-  hipError_t e = launch_fill_i64(d_bad_, n, INT64_MAX, s);
-  if (e == hipSuccess && any_f32_) e = launch_fill_i64(d_pctr_, 4, 0, s);
+  hipError_t e = launch_init_call(d_bad_, n, any_f32_ ? d_pctr_ : nullptr, s);
   if (e == hipSuccess)
     e = launch_setup(d_desc_, n, d_term_bases_, total_terms_, max_vars_, d_aux64_, d_aux32_, s);
   // fork: side streams start after the setup kernel
@@ -528,26 +527,23 @@ vecchia_status Batch::enqueue(hipStream_t s, bool allow_profile) {
     e = hipEventRecord(join_ev_[k], side_[k]);
     if (e == hipSuccess) e = hipStreamWaitEvent(s, join_ev_[k], 0);
   }
-  // FP32 instances: the terms promoted at set-up, in FP64 (a short persistent
-  // grid that finds nothing to do when no term was promoted)
   const bool redo = any_f32_ && ipt_max_ > 0;
-  if (e == hipSuccess && redo)
-    e = launch_qmc_promoted(f32_max_k_, d_desc_, n, d_term_bases_, d_aux64_, d_Z_, d_sums_, d_plist_, d_pctr_,
-                            plist_cap_, ipt_max_, s);
   if (e == hipSuccess)
     e = launch_finalize_terms(d_desc_, n, d_term_bases_, total_terms_, d_aux64_, d_sums_, d_term_res_, redo, s);
-  // then the terms whose FP32 estimate the finalize found heavy-tailed: FP64
-  // rows, FP64 items and their finalize (three grids that exit at once when
-  // the list is empty)
+  // FP32 instances: FP64 rows for the terms whose FP32 estimate the finalize
+  // found heavy-tailed, then these and the terms promoted at set-up in one FP64
+  // pass and their finalize (three grids that exit at once when the lists are
+  // empty). A pass of its own for the promoted terms before the finalize cost a
+  // small call 4 us.
   if (e == hipSuccess && redo)
     e = launch_setup_redo(d_desc_, n, d_term_bases_, max_vars_, d_aux64_, d_aux32_, d_plist_ + plist_cap_, d_pctr_ + 2,
                           plist_cap_, s);
   if (e == hipSuccess && redo)
-    e = launch_qmc_promoted(f32_max_k_, d_desc_, n, d_term_bases_, d_aux64_, d_Z_, d_sums_, d_plist_ + plist_cap_,
-                            d_pctr_ + 2, plist_cap_, ipt_max_, s);
+    e = launch_qmc_promoted(f32_max_k_, d_desc_, n, d_term_bases_, d_aux64_, d_Z_, d_sums_, d_plist_, d_pctr_,
+                            plist_cap_, ipt_max_, s);
   if (e == hipSuccess && redo)
-    e = launch_finalize_redo(d_desc_, n, d_term_bases_, d_aux64_, d_sums_, d_term_res_, d_plist_ + plist_cap_,
-                             d_pctr_ + 2, plist_cap_, s);
+    e = launch_finalize_redo(d_desc_, n, d_term_bases_, d_aux64_, d_sums_, d_term_res_, d_plist_, d_pctr_, plist_cap_,
+                             s);
   if (e == hipSuccess) e = launch_logsum(d_desc_, n, d_term_res_, s);
   if (e != hipSuccess) return hip_error(e, "kernel launch");
   return VECCHIA_OK;

@@ -38,8 +38,8 @@ struct InstDesc {
   // promote[t] (global term index) is 0, 1 (set-up) or 2 (re-run). A handed-over
   // term's FP64 rows take the place of its FP32 rows: prep_f64(I, i). plist holds
   // two lists of global term indices, plist_cap (= the batch's term count) each:
-  // [0, cap) the set-up promotions, [cap, 2 cap) the re-runs; pctr = {count,
-  // work counter} of each. Every qualifying term gets a slot, so a term's value
+  // [0, cap) the set-up promotions, [cap, 2 cap) the re-runs; pctr = {count of
+  // the first, work counter of their FP64 pass, count of the second}. Every qualifying term gets a slot, so a term's value
   // depends only on its instance. Shared by the batch.
   int32_t* promote;
   int32_t* plist;
@@ -117,7 +117,8 @@ __host__ __device__ inline double* prep_f64(const InstDesc& I, int64_t i) {
 // group > 1: query i's candidates are j < i - i mod group (no grid then).
 hipError_t launch_knn(const double* xs, const double* ys, int64_t D, int m, int32_t* nbr,
                       int32_t* kcnt, const KnnGrid* grid, hipStream_t s, int group = 1);
-hipError_t launch_fill_i64(int64_t* p, int64_t n, int64_t v, hipStream_t s);
+// The call's flags: n of bad[] to INT64_MAX and, if there, pctr[0..2] to 0.
+hipError_t launch_init_call(int64_t* bad, int64_t n, int64_t* pctr, hipStream_t s);
 // Copies `bytes` bytes of host memory to dst (device, 8-byte aligned) by kernels
 // that take them as arguments (no staging buffer, no memcpy node).
 hipError_t launch_store_bytes(void* dst, const void* src_host, size_t bytes, hipStream_t s);
@@ -141,8 +142,8 @@ hipError_t launch_qmc(int K, int precision, bool block, const InstDesc* d_insts,
                       int n_ranges, ItemSpan span, const Aux64* aux64, const Aux32* aux32,
                       const uint64_t* d_Z, double* sums, hipStream_t s);
 // The handed-over terms of FP32 instances in FP64: a persistent grid takes
-// (term, item) pairs from a device-side list (ctr[0] entries, at most cap;
-// ipt_max items per term at most; ctr[1] is the work counter) until none is left.
+// (term, item) pairs from the two device-side lists (InstDesc's plist and pctr;
+// at most cap terms together, ipt_max items per term at most) until none is left.
 // K: the most SOV steps of any term of the FP32 instances.
 hipError_t launch_qmc_promoted(int K, const InstDesc* d_insts, int n_inst, const int64_t* d_term_bases,
                                const Aux64* aux64, const uint64_t* d_Z, double* sums, const int32_t* list,
@@ -184,15 +185,15 @@ hipError_t launch_mixture_combine(const double* node_out, const MixWeights& mw, 
 // the log G and the root sum of squares of the SEs.
 hipError_t launch_mixture_combine_many(const double* node_out, const double* logw, int n_nodes, int64_t n_mix,
                                        double* out, double* total, hipStream_t s);
-// term_finalize over every term, then (redo_list non-null) over the re-run list
-// after its FP64 pass, then the per-instance sums. Without a list the first
-// pass hands nothing over.
+// term_finalize over every term, then over the two lists' terms after their FP64
+// pass, then the per-instance sums. Without allow_redo the first pass finalizes
+// every term and hands nothing over.
 hipError_t launch_finalize_terms(const InstDesc* d_insts, int n_inst, const int64_t* d_term_bases,
                                  int64_t total_terms, const Aux64* aux64, const double* sums,
                                  double2* term_res, bool allow_redo, hipStream_t s);
 hipError_t launch_finalize_redo(const InstDesc* d_insts, int n_inst, const int64_t* d_term_bases,
                                 const Aux64* aux64, const double* sums, double2* term_res,
-                                const int32_t* list, const int64_t* count, int64_t cap, hipStream_t s);
+                                const int32_t* list, const int64_t* ctr, int64_t cap, hipStream_t s);
 hipError_t launch_logsum(const InstDesc* d_insts, int n_inst, const double2* term_res, hipStream_t s);
 
 }  // namespace vecchia
