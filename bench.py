@@ -60,23 +60,26 @@ sys.path.insert(0, ROOT)
 # VALU instructions per SOV step counted on the main path of the kernel's
 # unrolled chain in its assembly (rare branches not taken); cross-checked on
 # every run against SQ_INSTS_VALU x 64 / steps of the committed counter profile
-# (within 2 %, the difference being each work item's set-up).
-SLOTS_PER_STEP_F32_K10 = 48.2
+# (within 3 %, the difference being each work item's set-up and the rare steps).
+SLOTS_PER_STEP_F32_K10 = 37.9
 # MI355X FP32 vector peak 157.3 TFLOP/s = 256 CUs x 2.4 GHz x 128 FMA lanes x 2:
 # 78.64e12 full-rate VALU lane-slots per second. FP64 vector peak 78.6 TFLOP/s.
 VALU_PEAK_TSLOTS = 256 * 2.4e9 * 128 / 1e12
 FP32_PEAK_TFLOPS = 157.3
 FP64_PEAK_TFLOPS = 78.6
-# Transcendental instructions per SOV step on that path (the rest are full-rate):
-# Phi^-1 takes a log2, a sqrt and a reciprocal, Phi a reciprocal and an exp2.
-TRANS_PER_STEP = {"exp": 1, "log": 1, "rcp": 2, "sqrt": 1}
+# Transcendental instructions per SOV step on that path: an exp2 per factor, and a
+# reciprocal for the last factor of the 10-step chain. The ceiling below takes the
+# rest as full-rate, which instructions with a scalar operand, compares and
+# conversions are not (about half of that rate): an upper bound.
+TRANS_PER_STEP = {"exp": 1.0, "rcp": 0.1}
 # rocprofv3 counter summaries of the QMC kernels at the headline workload; each
 # holds a `counters_json:` line with per-dispatch counters and the hash of the
 # kernel sources it was taken on (a changed kernel makes its figures stale).
 PMC_F32 = os.path.join(ROOT, "profiles", "qmc_f32_k10_uniform2500_pmc.md")
 PMC_F64 = os.path.join(ROOT, "profiles", "qmc_f64_k10_uniform2500_pmc.md")
-KERNEL_SOURCES = ["kernels_qmc.hip", "device_math_f32.h", "lattice.h", "fp32_math_coeffs.h", "vecchia_internal.h",
-                  "device_math_f64.h", "fp64_math_coeffs.h"]
+KERNEL_SOURCES = ["kernels_qmc.hip", "kernels_qmc_f32.hip", "kernels_qmc_f64.hip", "qmc_f32.h", "qmc_f64.h", "qmc_items.h",
+                  "lattice.h", "device_math_f32.h", "fp32_math_coeffs.h", "normal_tables_f32.h", "device_math_f64.h",
+                  "fp64_math_coeffs.h", "device_nodes_f64.h", "normal_tables.h", "vecchia_internal.h"]
 
 
 def kernel_source_sha():
@@ -742,8 +745,8 @@ def main():
                           FP64_PEAK_TFLOPS, 64)
     if c32.get("status") == "current":
         # the assembly count of the chain's main path against the executed instructions
-        c32["slots_check"] = ("ok" if abs(c32["valu_slots_per_step"] / SLOTS_PER_STEP_F32_K10 - 1.0) <= 0.02
-                              else "differs by more than 2 %")
+        c32["slots_check"] = ("ok" if abs(c32["valu_slots_per_step"] / SLOTS_PER_STEP_F32_K10 - 1.0) <= 0.03
+                              else "differs by more than 3 %")
     traffic = c32.get("traffic_bytes") if c32.get("status") == "current" else None
     res = {
         "metric": "Vecchia terms/s (m=10; plan + log-CDF per step)",

@@ -307,8 +307,9 @@ vecchia_status vecchia_batch_destroy(vecchia_batch_t batch);
 
 /* Kernel timing for measurement tools. While enabled, evaluations record HIP
  * events around every QMC launch on its stream (HIP graphs are then not used).
- * A QMC launch covers the terms of one conditioning-set size K in one
- * precision. vecchia_profile_read waits for the recorded launches of (K,
+ * A QMC launch then covers the terms of one conditioning-set size K in one
+ * precision (otherwise sizes with few terms share the next longer size's
+ * launch, with the same results). vecchia_profile_read waits for the recorded launches of (K,
  * precision) and returns their summed milliseconds, launch count and SOV steps
  * (sum over their terms of n_shifts * n_points * K). With K =
  * VECCHIA_PROFILE_FULL_SOV and VECCHIA_FP64 it reads vecchia_full_logcdf's
@@ -479,7 +480,8 @@ vecchia_status vecchia_probe_lattice(uint64_t seed, int64_t term, int32_t shift,
  * max_slots execution slots (each a stream with two side streams). Whenever a
  * slot is free, a scheduler thread admits the queued requests in arrival order
  * as one group - as many as fit in the arena, up to 64 requests - and runs
- * them as one batch: one QMC launch per conditioning-set size over all of them.
+ * them as one batch: one QMC launch per conditioning-set size over all of them
+ * (sizes with few terms share a launch).
  * Groups on different slots overlap on the device. A request's result is the
  * same alone and in any group. Errors: INVALID (budget 0, max_slots outside
  * 1..64), NOMEM, HIP. */
