@@ -101,9 +101,12 @@ __device__ __forceinline__ float tail_f32(float v) {
   return fast_exp2(p);
 }
 
-// phi_f32 with the ratio's coefficients in the instructions.
+// phi_f32 with the ratio's coefficients in the instructions. |v| enters capped at
+// 2^24: beyond, where a nearly singular block scales a limit by up to 1e8, the
+// denominator's a^5 would overflow and its reciprocal make R zero and the next
+// quantile NaN. The exponent f, which stops at -2^20, decides the value there.
 __device__ __forceinline__ float ratio_f32(float v, float* f) {
-  const float a = fabsf(v);
+  const float a = fminf(fabsf(v), 0x1p24f);
   *f = -(v * v);
   float p = kRP[4], q = kRQ[5];
   VECCHIA_FMAAK(p, a, kRP[3]);
@@ -144,7 +147,7 @@ struct Cold32 {
 // of the wave-steps are rare and k = 20, and 2.5% slower at k = 50.
 __device__ __noinline__ Cold32 cold32(float v, float awc) {
   float f, R = ratio_f32(v, &f);
-  f = fmaxf(f, -1048576.0f);
+  f = f < -1048576.0f ? -1048576.0f : f;   // a NaN stays
   const float fl = floorf(f);
   const float mm = fast_exp2(f - fl) * R;
   const bool neg = v <= 0.0f;
