@@ -78,7 +78,7 @@ TRANS_PER_STEP = {"exp": 1.0, "rcp": 0.1}
 PMC_F32 = os.path.join(ROOT, "profiles", "qmc_f32_k10_uniform2500_pmc.md")
 PMC_F64 = os.path.join(ROOT, "profiles", "qmc_f64_k10_uniform2500_pmc.md")
 KERNEL_SOURCES = ["kernels_qmc.hip", "kernels_qmc_f32.hip", "kernels_qmc_f64.hip", "qmc_f32.h", "qmc_f64.h", "qmc_items.h",
-                  "lattice.h", "device_math_f32.h", "fp32_math_coeffs.h", "normal_tables_f32.h", "device_math_f64.h",
+                  "xcd_map.h", "lattice.h", "device_math_f32.h", "fp32_math_coeffs.h", "normal_tables_f32.h", "device_math_f64.h",
                   "fp64_math_coeffs.h", "device_nodes_f64.h", "normal_tables.h", "vecchia_internal.h"]
 
 

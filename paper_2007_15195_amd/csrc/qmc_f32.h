@@ -340,7 +340,7 @@ __device__ __forceinline__ void item_f32(const Item& it, const Aux32* __restrict
   }
 }
 
-// Workgroup g of the grid takes the 4 items_per_wave consecutive items from
+// The workgroup in slot g of the grid (xcd_slot) takes the 4 items_per_wave consecutive items from
 // 4 items_per_wave g on, its waves one after another.
 template <int K, bool BLOCK>
 __global__ __launch_bounds__(64 * kF32Waves) __attribute__((amdgpu_waves_per_eu(f32_min_waves(K)))) void qmc_f32(
@@ -353,7 +353,7 @@ __global__ __launch_bounds__(64 * kF32Waves) __attribute__((amdgpu_waves_per_eu(
     cells[e] = reinterpret_cast<const float4*>(kQuantTable)[e < kQuantCells ? e : kQuantCells - 1];
   __syncthreads();
   const int wv = uniform(threadIdx.x >> 6);
-  int64_t g = item_base + block_item(0) * (int64_t)(kF32Waves * items_per_wave) + wv;
+  int64_t g = item_base + (int64_t)xcd_slot(blockIdx.x, gridDim.x) * (int64_t)(kF32Waves * items_per_wave) + wv;
   for (int j = 0; j < items_per_wave && g < item_end; ++j, g += kF32Waves) {
     const Item it = decode_item(insts, ranges, n_ranges, g);
     item_f32<K, BLOCK>(it, aux32, Zg, sums, sh[wv], cells);

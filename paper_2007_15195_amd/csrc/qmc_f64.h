@@ -174,7 +174,7 @@ __device__ __forceinline__ void item_f64(const Item& it, const Aux64* __restrict
   }
 }
 
-// Workgroup g of the grid takes the W items_per_wave consecutive items from
+// The workgroup in slot g of the grid (xcd_slot) takes the W items_per_wave consecutive items from
 // g W items_per_wave on, its waves one after another.
 template <int K>
 __global__ __launch_bounds__(64 * f64_waves(K)) __attribute__((amdgpu_waves_per_eu(f64_waves(K) / 2))) void qmc_f64(
@@ -186,7 +186,7 @@ __global__ __launch_bounds__(64 * f64_waves(K)) __attribute__((amdgpu_waves_per_
   __shared__ uint64_t sh[K > kF64AdvanceK ? W * K : 1];
   load_nodes(nodes);
   const int wv = uniform(threadIdx.x >> 6);
-  int64_t g = item_base + block_item(0) * (int64_t)(W * items_per_wave) + wv;
+  int64_t g = item_base + (int64_t)xcd_slot(blockIdx.x, gridDim.x) * (int64_t)(W * items_per_wave) + wv;
   for (int j = 0; j < items_per_wave && g < item_end; ++j, g += W) {
     const Item it = decode_item(insts, ranges, n_ranges, g);
     item_f64<K>(it, aux64, Zg, sums, reinterpret_cast<const double*>(it.I->prep) + it.i * it.I->prep_stride, nodes,

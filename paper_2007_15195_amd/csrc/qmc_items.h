@@ -1,6 +1,7 @@
 // Work items of the QMC kernels: (term, pass, shift, chunk), one wave each.
 #pragma once
 #include "vecchia_internal.h"
+#include "xcd_map.h"
 
 namespace vecchia {
 
@@ -24,19 +25,6 @@ __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirs
 // true when the predicate holds on some active lane (the ballot's mask is a
 // scalar, so the result is wave-uniform)
 __device__ __forceinline__ bool any_lane(bool p) { return __builtin_amdgcn_ballot_w64(p) != 0; }
-
-// The work item of this block. Consecutive blocks go to the chip's 8 XCDs in
-// turn (block b to XCD b mod 8), each with its own L2; the blocks of one XCD
-// take one contiguous range of the launch's items instead, so that the items
-// of one term (consecutive) share an L2 for the term's rows and for the lines
-// of their partial sums. A bijection of [0, gridDim.x) for any grid size; the
-// results do not depend on it.
-constexpr unsigned kXcds = 8;
-__device__ __forceinline__ int64_t block_item(int64_t item_base) {
-  const unsigned b = blockIdx.x, n = gridDim.x;
-  const unsigned x = b % kXcds, j = b / kXcds, q = n / kXcds, r = n % kXcds;
-  return item_base + (int64_t)(x * q + (x < r ? x : r) + j);
-}
 
 struct Item {
   const InstDesc* I;
