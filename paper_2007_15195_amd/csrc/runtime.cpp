@@ -246,6 +246,7 @@ Batch::~Batch() {
 // ms) and 17% slower (FP64, 30 steps in the 40-step kernel, of 6 waves a workgroup
 // in place of 8: 2.35 against 2.01 ms).
 constexpr int64_t kMergeItems = 16384;
+constexpr int64_t kMaxLaunchItems = 0x7fffffff;
 
 static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -266,7 +267,8 @@ vecchia_status Batch::create(const std::vector<vecchia_plan_s*>& plans,
   b->prep_off_.resize(n);
   int64_t tb = 0, sb = 0;
   size_t prep = 0;
-  std::map<std::tuple<int, bool, int>, std::vector<RangeDesc>> by_k;   // (precision, block, K) -> ranges
+  // (precision, FP32 joint terms, K, joint terms) -> ranges; the FP64 kernels take plain and joint terms alike
+  std::map<std::tuple<int, bool, int, bool>, std::vector<RangeDesc>> by_k;
   for (int j = 0; j < n; ++j) {
     vecchia_plan_s* P = plans[j];
     std::string why;
@@ -329,8 +331,7 @@ vecchia_status Batch::create(const std::vector<vecchia_plan_s*>& plans,
         r.K = k;
         r.items_per_term = passes * R * C;
         r.n_chunks = C;
-        // the FP64 kernels take plain and joint terms alike
-        by_k[{prec, prec == VECCHIA_FP32_LOOP && P->block > 0, k}].push_back(r);
+        by_k[{prec, prec == VECCHIA_FP32_LOOP && P->block > 0, k, P->block > 0}].push_back(r);
       }
       i = e;
     }
@@ -350,15 +351,19 @@ vecchia_status Batch::create(const std::vector<vecchia_plan_s*>& plans,
   // term's chain after its own k steps. Alone such a launch is a serial chain on
   // a fraction of the device: about 10 us of gaps and, at 10^4 points, 60 us of
   // latency each, one after another on the side streams (grid of 400 sites, m = 5:
-  // 107 -> 73 us a call). A length with more items keeps the kernel whose registers fit it.
+  // 107 -> 73 us a call). A length with more items keeps the kernel whose registers fit it,
+  // and one that would take a shared launch past kMaxLaunchItems has a launch of its own.
   // The launch with the most work runs on the caller's stream, the others beside it.
   for (auto it = by_k.rbegin(); it != by_k.rend(); ++it) {
     const int prec = std::get<0>(it->first), k = std::get<2>(it->first);
     const bool block = std::get<1>(it->first);
     int64_t items = 0;
     for (const RangeDesc& r : it->second) items += r.item_begin * r.items_per_term;
+    if (items > kMaxLaunchItems) return set_error(VECCHIA_E_INVALID, "more than 2^31-1 work items in one launch");
     Launch* L = b->launches_.empty() ? nullptr : &b->launches_.back();
-    if (!L || L->precision != prec || L->block != block || items >= kMergeItems) {
+    const bool share = L && L->precision == prec && L->block == block && (items < kMergeItems || L->spans.back().K == k) &&
+                       L->n_items + items <= kMaxLaunchItems;
+    if (!share) {
       Launch n;
       n.K = k;
       n.precision = prec;
@@ -382,7 +387,6 @@ vecchia_status Batch::create(const std::vector<vecchia_plan_s*>& plans,
     sp.items.end = L->n_items;
     L->sov_steps += sp.sov_steps;
     L->spans.push_back(sp);
-    if (L->n_items > 0x7fffffffLL) return set_error(VECCHIA_E_INVALID, "more than 2^31-1 work items in one launch");
   }
   std::stable_sort(b->launches_.begin(), b->launches_.end(),
                    [](const Launch& a, const Launch& c) { return a.sov_steps * (a.precision == VECCHIA_FP64 ? 8 : 1) >
