@@ -209,17 +209,21 @@ __global__ __launch_bounds__(256) void chol_step(double* __restrict__ A, double*
       }
 }
 
-// log Phi(t), t < -kPhiNodeMax (or NaN), with e = Phi(t): log e while e is above
+// log Phi(t), t < -kPhiNodeMax (or NaN, which stays), with e = Phi(t): log e while e is above
 // 1e-197; below, -t^2/2 + log((1 - 1/t^2 + 1*3/t^4 - ...) / (|t| sqrt(2 pi))), whose
-// first term left out is 3e-16 at t = -30.
+// first term left out is 3e-16 at t = -30; -inf where t^2 overflows.
 __device__ __forceinline__ double log_ncdf_low(double t, double e) {
   const double h = t * t, z = div64(1.0, h);
   double p = 1.0 - 13.0 * z;
 #pragma unroll
   for (int k = 11; k >= 1; k -= 2) p = __builtin_fma(-k * z, p, 1.0);
   const bool far = !(t > -30.0);
+  if (h == HUGE_VAL) return -HUGE_VAL;
   return log64(far ? div64(p, -2.50662827463100050242 * t) : e) - (far ? 0.5 * h : 0.0);
 }
+
+// The larger of the two; NaN if either is (a covariance that is not positive definite).
+__device__ __forceinline__ double max_nan(double a, double b) { return a >= b || a != a ? a : b; }
 
 // L: D x D with L^T strictly above the diagonal (what is on and below it is not
 // read as L); dinv: reciprocals of L's diagonal; b: D limits; Z: D - 1 generators;
@@ -463,7 +467,7 @@ __global__ __launch_bounds__(64 * kFsWaves) __attribute__((amdgpu_waves_per_eu(k
     point(tid, &r, &live);
     double mx = live ? s.lp : -HUGE_VAL;
 #pragma unroll
-    for (int o = 8; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 16));
+    for (int o = 8; o > 0; o >>= 1) mx = max_nan(mx, __shfl_xor(mx, o, 16));
     double x = (live && mx > -HUGE_VAL) ? exp(s.lp - mx) : 0.0;
 #pragma unroll
     for (int o = 8; o > 0; o >>= 1) x += __shfl_xor(x, o, 16);
@@ -500,7 +504,7 @@ int sov_tiles(int64_t all_tiles, int64_t D, int n_cu) {
 // One workgroup of 256: per shift r, l_r = log mean over points from the waves'
 // {max, sum exp} partials (strided partial reductions, then a fixed tree, so the
 // result does not depend on scheduling); then log F = log mean_r exp(l_r) and
-// the delta-method SE over shifts.
+// the delta-method SE over shifts. A NaN partial makes both NaN.
 __global__ __launch_bounds__(256) void full_final(const double2* __restrict__ part, int nblk, int R, int64_t N,
                                                   double* __restrict__ out) {
   __shared__ double red[256];
@@ -509,7 +513,7 @@ __global__ __launch_bounds__(256) void full_final(const double2* __restrict__ pa
     red[tid] = v;
     __syncthreads();
     for (int o = 128; o > 0; o >>= 1) {
-      if (tid < o) red[tid] = is_max ? fmax(red[tid], red[tid + o]) : red[tid] + red[tid + o];
+      if (tid < o) red[tid] = is_max ? max_nan(red[tid], red[tid + o]) : red[tid] + red[tid + o];
       __syncthreads();
     }
     const double res = red[0];
@@ -519,7 +523,7 @@ __global__ __launch_bounds__(256) void full_final(const double2* __restrict__ pa
   auto logmean = [&](int r) {
     const double2* __restrict__ pr = part + (int64_t)r * nblk;
     double mx = -HUGE_VAL;
-    for (int k = tid; k < nblk; k += 256) mx = fmax(mx, pr[k].x);
+    for (int k = tid; k < nblk; k += 256) mx = max_nan(mx, pr[k].x);
     const double M = tree(mx, true);
     if (!(M > -HUGE_VAL)) return M;
     double sm = 0.0;
@@ -530,7 +534,7 @@ __global__ __launch_bounds__(256) void full_final(const double2* __restrict__ pa
     return M + log(tree(sm, false)) - log((double)N);
   };
   double top = -HUGE_VAL;
-  for (int r = 0; r < R; ++r) top = fmax(top, logmean(r));
+  for (int r = 0; r < R; ++r) top = max_nan(top, logmean(r));
   double logF = top, se = __builtin_nan("");
   if (top > -HUGE_VAL) {
     double sum = 0.0;
