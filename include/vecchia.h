@@ -445,13 +445,19 @@ vecchia_status vecchia_calibrate_valu(void* hip_stream, double* rates_out);
  * univariate Phi and Phi^{-1} inside Genz's recursion), evaluated elementwise
  * so that tests pin them against library routines. in_dev: n doubles;
  * out_dev: n x 3 doubles {o0, o1, o2} (device). what:
- *   VECCHIA_PROBE_PHI_F32: the FP32 loop's factor at t = in: o0 = Phi(-|t|) as
- *     the main path forms it (2^(-v^2) R, v = kappa t in FP32), and the deep
- *     path's split o1 * 2^o2 of the same tail;
- *   VECCHIA_PROBE_NINV_F32: o0 = -Phi^{-1}(q) as the loop forms it from
- *     log2 q, q = in rounded to FP32 (0 < q <= 1/2), o1 = that q;
+ *   VECCHIA_PROBE_PHI_F32: the FP32 loop's CDF at t = in (v = kappa t in FP32):
+ *     o0 = Phi(-|t|) as a chain's last factor and the tail of a joint term form
+ *     it (2^(-v^2) R), and o1 * 2^o2 the rare path's split of the same tail;
+ *   VECCHIA_PROBE_TAIL_F32: o0 = Phi(-|t|) as the other factors form it, 2^p(|v|),
+ *     for |v| <= 3.41 (Phi >= 2^-15); beyond, where the loop takes the rare path,
+ *     it falls to 0;
+ *   VECCHIA_PROBE_RARE_F32: the rare path's whole step at t = in: the factor
+ *     Phi(t) = o1 * 2^o2 and o0 = -Phi^{-1}(Phi(t) / 2);
+ *   VECCHIA_PROBE_NINV_F32: o0 = -Phi^{-1}(q), q = in rounded to FP32
+ *     (0 < q <= 1/2), o1 = that q: from the loop's table for q >= 2^-15, from
+ *     log2 q below;
  *   VECCHIA_PROBE_NINV_LOG2_F32: o0 = -Phi^{-1}(2^in) from the FP32 log2 in
- *     (the split path, whose exponents reach -2^20);
+ *     (the rare path, whose exponents reach -2^20);
  *   VECCHIA_PROBE_PHI_F64 / VECCHIA_PROBE_NINV_F64: o0 = the FP64 loop's
  *     normcdf(in) / normcdfinv(in).
  * Asynchronous on hip_stream. Errors: INVALID (unknown what, n outside
@@ -461,6 +467,8 @@ vecchia_status vecchia_calibrate_valu(void* hip_stream, double* rates_out);
 #define VECCHIA_PROBE_NINV_LOG2_F32 2
 #define VECCHIA_PROBE_PHI_F64 3
 #define VECCHIA_PROBE_NINV_F64 4
+#define VECCHIA_PROBE_TAIL_F32 5
+#define VECCHIA_PROBE_RARE_F32 6
 vecchia_status vecchia_probe_math(int32_t what, int64_t n, const double* in_dev, double* out_dev,
                                   void* hip_stream);
 

@@ -8,7 +8,7 @@ node of a cell is its midpoint q_i, and holds z_i = -Phi^{-1}(q_i) and
 above). CDF nodes: a_i = i / 128, i = -1088 .. 1088 (|a| <= 8.5), each holding
 Phi(a_i) and phi(a_i).
 
-normal_tables_f32.h, for the FP32 loop (device_math_f32.h): the quantile
+normal_tables_f32.h, for the FP32 loop (qmc_f32.h): the quantile
 z = -Phi^{-1}(q) on q in [2^-15, 1/2] as one quadratic per cell of 32 per
 octave, (c0, c1, c2, midpoint), minimax in absolute error, each coefficient
 rounded to FP32 before the lower ones are fitted; and the coefficients of

@@ -48,22 +48,18 @@ __device__ __forceinline__ double lattice_coord_f64(uint64_t U) {
   return fabs(t - __longlong_as_double((long long)((uint64_t)one << 32)));
 }
 
-// FP32 coordinate of U, from its upper 32 bits only: with s = U_hi - 2^31 as a
-// signed 32-bit integer, the cell is c = |s| >> 8 for s >= 0 and
-// (|s| - 1) >> 8 for s < 0, and w = (c + 1/2) 2^-23, the midpoint of the 2^-23
+// 1 - w for the FP32 coordinate w of U, from its upper 32 bits only: with
+// s = U_hi - 2^31 as a signed 32-bit integer, the cell is c = |s| >> 8 for s >= 0
+// and (|s| - 1) >> 8 for s < 0, and w = (c + 1/2) 2^-23, the midpoint of the 2^-23
 // cell of the baker-transformed point (within 2^-24 of the FP64 coordinate;
 // exactly its cell unless U's low 40 bits are all zero). With
-// g = (signed U_hi) >> 8 this is w = 1 - |g + 1/2| 2^-23, so 1 - w = |g + 1/2| 2^-23;
-// both are exact in FP32.
-struct CoordF32 {
-  float w, wc;   // w and 1 - w
-};
-__device__ __forceinline__ CoordF32 lattice_coord_f32(uint32_t hi) {
+// g = (signed U_hi) >> 8 this is w = 1 - |g + 1/2| 2^-23; w and 1 - w are exact in
+// FP32. c24 = 2^-24, in a register that the caller keeps.
+__device__ __forceinline__ float lattice_complement_f32(uint32_t hi, float c24) {
   const float g = (float)((int32_t)hi >> 8);
-  CoordF32 c;
-  c.wc = fabsf(fmaf(g, 0x1p-23f, 0x1p-24f));
-  c.w = 1.0f - c.wc;
-  return c;
+  float wc;
+  __asm__("v_fmamk_f32 %0, %1, %2, %3" : "=v"(wc) : "v"(g), "i"(__builtin_bit_cast(uint32_t, 0x1p-23f)), "v"(c24));
+  return fabsf(wc);
 }
 
 }  // namespace vecchia

@@ -6,11 +6,10 @@
 
 #include <cmath>
 
-#include "device_math_f32.h"
 #include "device_math_f64.h"
 #include "device_nodes_f64.h"
 #include "lattice.h"
-#include "normal_tables_f32.h"
+#include "qmc_f32.h"
 #include "runtime.h"
 #include "vecchia.h"
 
@@ -22,34 +21,32 @@ constexpr int kProbeThreads = 256;
 // what (see vecchia_probe_math): out has 3 doubles per input
 __global__ __launch_bounds__(kProbeThreads) void probe_math(int what, int64_t n, const double* __restrict__ in,
                                                             double* __restrict__ out) {
+  __shared__ float4 cells[kQuantSlots];
+  load_cells<kProbeThreads>(cells);
   const int64_t i = (int64_t)blockIdx.x * kProbeThreads + threadIdx.x;
   if (i >= n) return;
   const double x = in[i];
+  const float v = (float)(x * kPhiScale);   // the FP32 loop's argument kappa t at t = x
   double o0 = 0.0, o1 = 0.0, o2 = 0.0;
   if (what == VECCHIA_PROBE_PHI_F32) {
-    // the SOV loop's factor at t = x: v = kappa t in FP32; the smaller tail as
-    // the main path forms it, and as the deep path splits it (em * 2^fl)
-    const float v = (float)(x * kPhiScale);
-    const PhiParts ph = phi_f32(v);
-    const float f = fmaxf(ph.f, -1048576.0f);
-    const float fl = floorf(f);
-    o0 = ph.m;
-    o1 = fast_exp2(f - fl) * ph.R;
-    o2 = fl;
+    // the smaller tail as a chain's last factor has it, and as the rare path splits it
+    o0 = phi_f32(v).m;
+    const Cold32 c = cold32(-fabsf(v), 0.5f);
+    o1 = c.em;
+    o2 = c.en;
+  } else if (what == VECCHIA_PROBE_TAIL_F32) {
+    o0 = tail_f32(v);
+  } else if (what == VECCHIA_PROBE_RARE_F32) {
+    const Cold32 c = cold32(v, 0.5f);
+    o0 = c.y;
+    o1 = c.em;
+    o2 = c.en;
   } else if (what == VECCHIA_PROBE_NINV_F32) {
-    // the SOV loop's quantile of q = x (0 < q <= 1/2, rounded to FP32):
-    // z = -Phi^{-1}(q) from its cell, below the cells from log2 q
+    // from its cell, below the cells from log2 q
     const float q = (float)x;
-    if (q >= 0x1p-15f) {
-      const float* c = kQuantTable[((__builtin_bit_cast(uint32_t, q) >> 14) & 0x1ff0u) / 16];
-      const float d = q - c[3];
-      o0 = fmaf(fmaf(c[2], d, c[1]), d, c[0]);
-    } else {
-      o0 = ninv_tail_from_log2_split(fast_log2(q));
-    }
+    o0 = q >= kQuantMin ? quant_f32(cells, q) : ninv_tail_from_log2_split(fast_log2(q));
     o1 = q;
   } else if (what == VECCHIA_PROBE_NINV_LOG2_F32) {
-    // the split path's quantile from log2 q = x directly (its exponents reach -2^20)
     o0 = ninv_tail_from_log2_split((float)x);
   } else if (what == VECCHIA_PROBE_PHI_F64) {
     // as the FP64 loop: the node table, the fitted ratio below it
@@ -71,7 +68,7 @@ __global__ __launch_bounds__(kProbeThreads) void probe_lattice(const uint64_t* _
   if (i >= n) return;
   const uint64_t U = (uint64_t)(i + 1) * Z[dim] + lattice_shift(seed, term, r, dim, second != 0);
   if (w64) w64[i] = lattice_coord_f64(U);
-  if (w32) w32[i] = lattice_coord_f32((uint32_t)(U >> 32)).w;
+  if (w32) w32[i] = 1.0f - lattice_complement_f32((uint32_t)(U >> 32), 0x1p-24f);
 }
 
 }  // namespace
@@ -82,7 +79,7 @@ extern "C" {
 vecchia_status vecchia_probe_math(int32_t what, int64_t n, const double* in_dev, double* out_dev,
                                   void* hip_stream) {
   using namespace vecchia;
-  if (what < VECCHIA_PROBE_PHI_F32 || what > VECCHIA_PROBE_NINV_F64)
+  if (what < VECCHIA_PROBE_PHI_F32 || what > VECCHIA_PROBE_RARE_F32)
     return set_error(VECCHIA_E_INVALID, "unknown probe");
   if (n < 0 || n > (1LL << 30)) return set_error(VECCHIA_E_INVALID, "n must be in 0..2^30");
   if (n == 0) return VECCHIA_OK;

@@ -77,13 +77,10 @@ constexpr int f32_min_waves(int K) { return K <= 12 ? 8 : K <= 18 ? 6 : K <= 24 
 using ScalarGen32 = const __attribute__((address_space(4))) uint64_t*;
 using ScalarRows32 = const __attribute__((address_space(4))) float*;
 
-// p * a + literal and a * literal + c, the coefficients in the instruction. No
-// operand may come straight from exp, log, rcp or sqrt: the wait state that
+// p * a + literal, the coefficient in the instruction. No operand may come straight from exp, log, rcp or sqrt: the wait state that
 // gfx950 wants behind those is not inserted before inline assembly.
 #define VECCHIA_FMAAK(p, a, k)                                                                                      \
   __asm__("v_fmaak_f32 %0, %1, %2, %3" : "=v"(p) : "v"(p), "v"(a), "i"(__builtin_bit_cast(uint32_t, (float)(k))))
-#define VECCHIA_FMAMK(d, a, k, c) \
-  __asm__("v_fmamk_f32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "i"(__builtin_bit_cast(uint32_t, (float)(k))), "v"(c))
 
 // Phi(-|v| / kappa) for |v| <= 3.41 (Phi >= 2^-15); beyond it falls to 0 with an
 // absolute error below 5e-11.
@@ -101,7 +98,7 @@ __device__ __forceinline__ float tail_f32(float v) {
   return fast_exp2(p);
 }
 
-// phi_f32 with the ratio's coefficients in the instructions. |v| enters capped at
+// R = erfcx(|t| / sqrt 2) / 2, t = v / kappa, with f = -v^2. |v| enters capped at
 // 2^24: beyond, where a nearly singular block scales a limit by up to 1e8, the
 // denominator's a^5 would overflow and its reciprocal make R zero and the next
 // quantile NaN. The exponent f, which stops at -2^20, decides the value there.
@@ -120,13 +117,30 @@ __device__ __forceinline__ float ratio_f32(float v, float* f) {
   VECCHIA_FMAAK(q, a, kRQ[0]);
   return p * fast_rcp(q);
 }
-__device__ __forceinline__ PhiParts phi_f32_lit(float v) {
+// Phi(t) from v = kappa t, as e = em (exact unless em is split further by the
+// caller) with the smaller tail m = Phi(-|t|) = 2^f R, f = -v^2.
+struct PhiParts {
+  float em;   // Phi(t)
+  float m;    // Phi(-|t|)
+  float f;    // -v^2
+  float R;    // erfcx(|t| / sqrt 2) / 2
+  bool neg;   // t <= 0
+};
+__device__ __forceinline__ PhiParts phi_f32(float v) {
   PhiParts o;
   o.R = ratio_f32(v, &o.f);
   o.m = fast_exp2(o.f) * o.R;
   o.neg = v <= 0.0f;
   o.em = o.neg ? o.m : 1.0f - o.m;
   return o;
+}
+
+// The cells to LDS, by a workgroup of kThreads.
+template <int kThreads>
+__device__ __forceinline__ void load_cells(float4* cells) {
+  for (int e = threadIdx.x; e < kQuantSlots; e += kThreads)
+    cells[e] = reinterpret_cast<const float4*>(kQuantTable)[e < kQuantCells ? e : kQuantCells - 1];
+  __syncthreads();
 }
 
 // -Phi^{-1}(q) from the cells; any q outside their range addresses some slot.
@@ -194,11 +208,7 @@ __device__ __forceinline__ void steps_f32(Chain32<K>& s, uint64_t* U, const uint
   } else {
     hi = (uint32_t)(((uint64_t)pt * Z[A - 1] + sh[A - 1]) >> 32);
   }
-  // lattice_coord_f32: 1 - w = |g + 1/2| 2^-23, exact
-  const float g = (float)((int32_t)hi >> 8);
-  float wc;
-  VECCHIA_FMAMK(wc, g, 0x1p-23f, c24);
-  wc = fabsf(wc);
+  const float wc = lattice_complement_f32(hi, c24);    // 1 - w
   const float um = fmaf(-wc, s.em, s.em);              // u = w e
   const float qt = fminf(um, fmaf(wc, s.em, s.m));     // min(u, 1 - u)
   float y = __builtin_copysignf(quant_f32(cells, qt), 0.5f - um);
@@ -242,7 +252,7 @@ __device__ __forceinline__ void steps_f32(Chain32<K>& s, uint64_t* U, const uint
     if (A == k) return;
     if (BLOCK && A >= sp) {
       // a factor of the numerator's tail: its complement to full relative accuracy
-      const PhiParts ph = phi_f32_lit(v);
+      const PhiParts ph = phi_f32(v);
       s.em = ph.em;
       s.m = ph.m;
       s.cc = fmaf(ph.neg ? 1.0f - ph.em : ph.m, 1.0f - s.cc, s.cc);
@@ -285,9 +295,9 @@ __device__ __forceinline__ void item_f32(const Item& it, const Aux32* __restrict
   __asm__ volatile("" : "+v"(c24));
   double acc_num = 0.0, acc_den = 0.0, acc_cnum = 0.0;
   for (int p0 = p_begin; p0 <= p_last; p0 += 64) {
-    // compiler-only barrier: the rows are re-read from LDS in every iteration
-    // instead of being held in registers across the loop; the scalars are opaque
-    // so that a step compares and loads in place
+    // opaque per iteration: the rows and generators come through scalar loads
+    // where a step uses them instead of being held across the loop, and k and sp
+    // are compared in place
     __asm__ volatile("" : "+s"(Z_u), "+s"(rows_u), "+s"(k), "+s"(sp)::"memory");
     Chain32<K> s;
     s.em = ax.em0;
@@ -306,7 +316,7 @@ __device__ __forceinline__ void item_f32(const Item& it, const Aux32* __restrict
     steps_f32<1, K, BLOCK>(s, U, sh, (ScalarGen32)Z_u, (ScalarRows32)rows_u, cells, c24, ax, split0, k, sp, (uint32_t)(p0 + lane));
     // the last factor, to full accuracy; its exponent and the product's are 0
     // but for rare lanes
-    const PhiParts ph = phi_f32_lit(s.v);
+    const PhiParts ph = phi_f32(s.v);
     double em = (double)ph.em, ec = (double)(ph.neg ? 1.0f - ph.em : ph.m);
     double den = (double)(BLOCK ? s.dm : s.qm), num = (double)s.qm;
     const uint64_t odd = __builtin_amdgcn_ballot_w64(s.v < -kDeepV) | __builtin_amdgcn_ballot_w64((s.qe | s.de) != 0);
@@ -349,9 +359,7 @@ __global__ __launch_bounds__(64 * kF32Waves) __attribute__((amdgpu_waves_per_eu(
     int64_t item_end, int items_per_wave) {
   __shared__ float4 cells[kQuantSlots];
   __shared__ uint64_t sh[kF32Waves][K > kF32AdvanceK ? K : 1];
-  for (int e = threadIdx.x; e < kQuantSlots; e += 64 * kF32Waves)
-    cells[e] = reinterpret_cast<const float4*>(kQuantTable)[e < kQuantCells ? e : kQuantCells - 1];
-  __syncthreads();
+  load_cells<64 * kF32Waves>(cells);
   const int wv = uniform(threadIdx.x >> 6);
   int64_t g = item_base + (int64_t)xcd_slot(blockIdx.x, gridDim.x) * (int64_t)(kF32Waves * items_per_wave) + wv;
   for (int j = 0; j < items_per_wave && g < item_end; ++j, g += kF32Waves) {

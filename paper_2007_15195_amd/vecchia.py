@@ -444,6 +444,7 @@ def vecchia_calibrate_valu(stream=None) -> dict:
 
 VECCHIA_PROBE_PHI_F32, VECCHIA_PROBE_NINV_F32, VECCHIA_PROBE_NINV_LOG2_F32 = 0, 1, 2
 VECCHIA_PROBE_PHI_F64, VECCHIA_PROBE_NINV_F64 = 3, 4
+VECCHIA_PROBE_TAIL_F32, VECCHIA_PROBE_RARE_F32 = 5, 6
 
 
 def vecchia_probe_math(what: int, x, out, stream=None) -> None:
