@@ -54,6 +54,8 @@
 // workgroup is four waves with their own items around one table (8 KB), eight
 // workgroups to a compute unit.
 #pragma once
+#include <utility>
+
 #include "vecchia_internal.h"
 
 #include "device_math_f32.h"
@@ -386,6 +388,15 @@ hipError_t launch_f32_k(const InstDesc* insts, const RangeDesc* ranges, int n_ra
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
+}
+
+// The launch of the kernel for kc steps, among the sizes SizeOf(0), SizeOf(1), ...
+template <int (*SizeOf)(int), bool BLOCK, int... Is>
+hipError_t run_f32(int kc, const InstDesc* insts, const RangeDesc* ranges, int n_ranges, ItemSpan span,
+                   const Aux32* aux32, const uint64_t* Z, double* sums, hipStream_t s, std::integer_sequence<int, Is...>) {
+  hipError_t e = hipErrorInvalidValue;
+  ((kc == SizeOf(Is) ? (e = launch_f32_k<SizeOf(Is), BLOCK>(insts, ranges, n_ranges, span, aux32, Z, sums, s), 0) : 0), ...);
+  return e;
 }
 
 }  // namespace

@@ -30,6 +30,8 @@
 // compute unit's LDS (64 KB of tables each); W is 8, 6 or 4, the most waves
 // (4, 3 or 2 per SIMD) whose registers hold 2K doubles without spilling.
 #pragma once
+#include <utility>
+
 #include "vecchia_internal.h"
 
 #include "device_math_f64.h"
@@ -288,6 +290,27 @@ hipError_t launch_promoted_k(const InstDesc* insts, int n_inst, const int64_t* t
   hipLaunchKernelGGL(qmc_promoted<K>, dim3(grid), dim3(64 * W), 0, s, insts, n_inst, term_bases, aux64, Z, sums, list,
                      ctr, cap, ipt_max);
   return hipGetLastError();
+}
+
+// The launch of the kernel for kc steps, among the sizes SizeOf(0), SizeOf(1), ...
+template <int (*SizeOf)(int), int... Is>
+hipError_t run_f64(int kc, const InstDesc* insts, const RangeDesc* ranges, int n_ranges, ItemSpan span,
+                   const Aux64* aux64, const uint64_t* Z, double* sums, hipStream_t s, std::integer_sequence<int, Is...>) {
+  hipError_t e = hipErrorInvalidValue;
+  ((kc == SizeOf(Is) ? (e = launch_f64_k<SizeOf(Is)>(insts, ranges, n_ranges, span, aux64, Z, sums, s), 0) : 0), ...);
+  return e;
+}
+
+template <int (*SizeOf)(int), int... Is>
+hipError_t run_promoted(int kc, const InstDesc* insts, int n_inst, const int64_t* term_bases, const Aux64* aux64,
+                        const uint64_t* Z, double* sums, const int32_t* list, int64_t* ctr, int64_t cap, int ipt_max,
+                        hipStream_t s, std::integer_sequence<int, Is...>) {
+  hipError_t e = hipErrorInvalidValue;
+  ((kc == SizeOf(Is)
+        ? (e = launch_promoted_k<SizeOf(Is)>(insts, n_inst, term_bases, aux64, Z, sums, list, ctr, cap, ipt_max, s), 0)
+        : 0),
+   ...);
+  return e;
 }
 
 }  // namespace
