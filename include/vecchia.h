@@ -401,9 +401,12 @@ vecchia_status vecchia_mixbatch_destroy(vecchia_mixbatch_t mb);
  * log Phi. Lattice: Z_j from the first D-1 primes; the shift of dimension j in
  * replicate r is SplitMix64 output 2^63 + r 2^32 + j of q->seed.
  * out_dev = {log F, delta-method SE over the shifts} (device); NaN when the
- * covariance is not positive definite. q->precision must be VECCHIA_FP64 and
- * q->n_shifts at most 1024. Workspace D^2 + (D-1) N R doubles, kept in the
- * plan and grown on demand (at most 64 GB; D <= 40000). Asynchronous on
+ * covariance is not positive definite (or a threshold NaN). q->precision must
+ * be VECCHIA_FP64 and q->n_shifts at most 1024. D is at most 40000 and
+ * 8 (D^2 + D + (D-1) N R) + 16 R (ceil(N / 16) + 3) bytes at most 64e9. The
+ * workspace, kept in the plan and grown on demand, holds D^2 + 2 D doubles and
+ * at most 16 D doubles for every 16 points of a shift or part of 16 (points are
+ * taken 16 at a time, up to 9 such tiles to a workgroup). Asynchronous on
  * hip_stream. Errors: INVALID (censored plan, FP32, sizes), NOMEM, HIP. */
 vecchia_status vecchia_full_logcdf(vecchia_plan_t plan, const double* x_dev, double scale,
                                    const vecchia_cov* cov_override, const vecchia_qmc* q, double* out_dev,

@@ -99,6 +99,10 @@ __device__ __forceinline__ double lane_value(double v, int lane) {   // lane uni
 // chain of launches: 26 us each at 2,500 dimensions, 79 of them, against 50 us
 // for the three launches (factor, rows, update) of a panel before. (The factor's
 // rows by LDS broadcasts instead of lane reads: 31 us, its registers spill.)
+// Rows are multiplied by the pivots' reciprocals where a division would round once:
+// over 16 instances of 400 to 1,000 dimensions log F is off from 25-digit values by
+// 4.0e-15 (exponential) and 1.6e-15 (Matern with a nugget) relative on average, the
+// three launches before, which divided, by 4.0e-15 and 2.7e-15.
 __global__ __launch_bounds__(256) void chol_step(double* __restrict__ A, double* __restrict__ dinv, int64_t D,
                                                  int64_t k0, int n) {
   const int64_t base = k0 + n;
@@ -578,6 +582,7 @@ extern "C" vecchia_status vecchia_full_logcdf(vecchia_plan_t plan, const double*
   const int64_t D = plan->D, N = q->n_points, R = q->n_shifts;
   const int64_t S = N * R;   // points
   // the limit: A (D x D), b (D), (D - 1) y for each of the S points and the partials
+  // (what is allocated below pads a shift's points to 16: at most 15 R D doubles more, 4.9 GB)
   const int64_t n_head = D * D + D + std::max<int64_t>(1, D - 1) * S;
   const int64_t n_head_even = n_head + (n_head & 1);
   const double bytes = 8.0 * (double)n_head_even + 16.0 * R * ((N + kFsWavePts - 1) / kFsWavePts + 3);

@@ -34,8 +34,9 @@
 // step now and with one-wave workgroups, fitted ratios and rows in LDS:
 // k = 10: 27.0 (38.8); k = 20: 31.8 (43.1); k = 31: 39.8 (56.7); k = 63: 57.7 (147).
 //
-// Rare lanes (cold32, cold32_first; 0.4% of wave-steps with thresholds near the
-// 0.9 quantile, up to 20% with rough thresholds on a smooth field): factors are
+// Rare lanes (cold32, cold32_first; 0.7% of wave-steps with thresholds near the
+// 0.9 quantile, 3% to 15% with rough thresholds on a smooth field, counted by the
+// 72 vector instructions that such a step adds): factors are
 // e = em * 2^en, with en = 0 except for a rare lane's lower-tail factors, which
 // keep 2^floor(-v^2) in en so that em stays in [R, 2R). The product of the factors is
 // qm * 2^qe (qe an integer): a common factor is at least 2^-15, so qm is
@@ -84,8 +85,13 @@ using ScalarRows32 = const __attribute__((address_space(4))) float*;
 #define VECCHIA_FMAAK(p, a, k)                                                                                      \
   __asm__("v_fmaak_f32 %0, %1, %2, %3" : "=v"(p) : "v"(p), "v"(a), "i"(__builtin_bit_cast(uint32_t, (float)(k))))
 
-// Phi(-|v| / kappa) for |v| <= 3.41 (Phi >= 2^-15); beyond it falls to 0 with an
-// absolute error below 5e-11.
+// Phi(-|v| / kappa) for |v| <= 3.41 (Phi >= 2^-15), with a relative error below
+// 0.9e-6 for |v| < 0.5, rising to 1.8e-6 at 3.4 (the fit's 0.8e-6 and the rounding
+// of an exponent near -15), 5.6e-7 in the mean square; beyond it falls to 0 with an
+// absolute error below 5e-11. (The (3,4) ratio before: 1.4e-6 and 6.7e-7. A
+// polynomial of degree 10 has 1.3e-6 and 2.0e-7 for two more instructions a step;
+// one of degree 9 rises beyond the range; other weights at degree 8 take the 1.8e-6
+// down to 1.4e-6 and the error for |v| < 1, where most factors lie, up by a third.)
 __device__ __forceinline__ float tail_f32(float v) {
   const float a = fabsf(v);
   float p = kTailPoly[8];
@@ -145,7 +151,8 @@ __device__ __forceinline__ void load_cells(float4* cells) {
   __syncthreads();
 }
 
-// -Phi^{-1}(q) from the cells; any q outside their range addresses some slot.
+// -Phi^{-1}(q) from the cells, absolute error below 4e-7; any q outside their range
+// addresses some slot.
 __device__ __forceinline__ float quant_f32(const float4* cells, float q) {
   const uint32_t off = (__builtin_bit_cast(uint32_t, q) >> 14) & 0x1ff0u;
   const float4 c = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(cells) + off);
