@@ -365,12 +365,12 @@ template <int K, bool BLOCK>
 __global__ __launch_bounds__(64 * kF32Waves) __attribute__((amdgpu_waves_per_eu(f32_min_waves(K)))) void qmc_f32(
     const InstDesc* __restrict__ insts, const RangeDesc* __restrict__ ranges, int n_ranges,
     const Aux32* __restrict__ aux32, const uint64_t* __restrict__ Zg, double* __restrict__ sums, int64_t item_base,
-    int64_t item_end, int items_per_wave) {
+    int64_t item_end, int items_per_wave, int even) {
   __shared__ float4 cells[kQuantSlots];
   __shared__ uint64_t sh[kF32Waves][K > kF32AdvanceK ? K : 1];
   load_cells<64 * kF32Waves>(cells);
   const int wv = uniform(threadIdx.x >> 6);
-  int64_t g = item_base + (int64_t)xcd_slot(blockIdx.x, gridDim.x) * (int64_t)(kF32Waves * items_per_wave) + wv;
+  int64_t g = item_base + (int64_t)xcd_slot(blockIdx.x, gridDim.x, even != 0) * (int64_t)(kF32Waves * items_per_wave) + wv;
   for (int j = 0; j < items_per_wave && g < item_end; ++j, g += kF32Waves) {
     const Item it = decode_item(insts, ranges, n_ranges, g);
     item_f32<K, BLOCK>(it, aux32, Zg, sums, sh[wv], cells);
@@ -390,7 +390,7 @@ hipError_t launch_f32_k(const InstDesc* insts, const RangeDesc* ranges, int n_ra
     const int64_t left = (span.end - b + block_items - 1) / block_items;
     const unsigned n = (unsigned)(left < kMaxBlocks ? left : kMaxBlocks);
     hipLaunchKernelGGL((qmc_f32<K, BLOCK>), dim3(n), dim3(64 * kF32Waves), 0, s, insts, ranges, n_ranges, aux32, Z, sums,
-                       b, span.end, (int)per);
+                       b, span.end, (int)per, (int)span.even);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -182,13 +182,13 @@ template <int K>
 __global__ __launch_bounds__(64 * f64_waves(K)) __attribute__((amdgpu_waves_per_eu(f64_waves(K) / 2))) void qmc_f64(
     const InstDesc* __restrict__ insts, const RangeDesc* __restrict__ ranges, int n_ranges,
     const Aux64* __restrict__ aux64, const uint64_t* __restrict__ Zg, double* __restrict__ sums, int64_t item_base,
-    int64_t item_end, int items_per_wave) {
+    int64_t item_end, int items_per_wave, int even) {
   constexpr int W = f64_waves(K);
   __shared__ __align__(16) double nodes[2 * kNormNodes];
   __shared__ uint64_t sh[K > kF64AdvanceK ? W * K : 1];
   load_nodes(nodes);
   const int wv = uniform(threadIdx.x >> 6);
-  int64_t g = item_base + (int64_t)xcd_slot(blockIdx.x, gridDim.x) * (int64_t)(W * items_per_wave) + wv;
+  int64_t g = item_base + (int64_t)xcd_slot(blockIdx.x, gridDim.x, even != 0) * (int64_t)(W * items_per_wave) + wv;
   for (int j = 0; j < items_per_wave && g < item_end; ++j, g += W) {
     const Item it = decode_item(insts, ranges, n_ranges, g);
     item_f64<K>(it, aux64, Zg, sums, reinterpret_cast<const double*>(it.I->prep) + it.i * it.I->prep_stride, nodes,
@@ -273,7 +273,7 @@ hipError_t launch_f64_k(const InstDesc* insts, const RangeDesc* ranges, int n_ra
     const int64_t left = (span.end - b + block_items - 1) / block_items;
     const unsigned n = (unsigned)(left < max_blocks ? left : max_blocks);
     hipLaunchKernelGGL(qmc_f64<K>, dim3(n), dim3(64 * W), 0, s, insts, ranges, n_ranges, aux64, Z, sums, b, span.end,
-                       (int)per);
+                       (int)per, (int)span.even);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

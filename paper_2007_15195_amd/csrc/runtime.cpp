@@ -247,6 +247,12 @@ Batch::~Batch() {
 // in place of 8: 2.35 against 2.01 ms).
 constexpr int64_t kMergeItems = 16384;
 constexpr int64_t kMaxLaunchItems = 0x7fffffff;
+// Items from which a launch of one length of one instance is even (xcd_map.h): 8
+// rounds of the wave slots. In fewer rounds the last one counts more than the L2,
+// and it is shorter when every XCD ends with the short chains at the list's end
+// (2,500 sites in triples, one round: 492 us with stripes, 508 with eighths).
+constexpr int64_t kEvenItems = 65536;
+static bool even_items(int64_t most, int64_t items) { return items >= kEvenItems && most >= items - items / 64; }
 
 static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -370,13 +376,15 @@ vecchia_status Batch::create(const std::vector<vecchia_plan_s*>& plans,
       n.block = block;
       n.range_off = (int)b->ranges_.size();
       n.n_ranges = 0;
-      n.n_items = n.sov_steps = 0;
+      n.n_items = n.sov_steps = n.most = 0;
       b->launches_.push_back(n);
       L = &b->launches_.back();
     }
-    Span sp{k, {L->n_items, 0}, 0};
+    Span sp{k, {L->n_items, 0, false}, 0};
+    int64_t most = 0;   // of one range
     for (RangeDesc r : it->second) {
       const int64_t nterms = r.item_begin;
+      most = std::max(most, nterms * r.items_per_term);
       r.item_begin = L->n_items;
       L->n_items += nterms * r.items_per_term;
       sp.sov_steps += nterms * (int64_t)b->desc_[r.inst].passes * b->desc_[r.inst].n_shifts *
@@ -385,6 +393,8 @@ vecchia_status Batch::create(const std::vector<vecchia_plan_s*>& plans,
       ++L->n_ranges;
     }
     sp.items.end = L->n_items;
+    sp.items.even = even_items(most, items);
+    L->most = std::max(L->most, most);
     L->sov_steps += sp.sov_steps;
     L->spans.push_back(sp);
   }
@@ -518,7 +528,7 @@ vecchia_status Batch::enqueue(hipStream_t s, bool allow_profile) {
                         d_Z_, d_sums_, ls);
     };
     if (!prof) {
-      e = qmc(L.K, {0, L.n_items});
+      e = qmc(L.K, {0, L.n_items, even_items(L.most, L.n_items)});
       continue;
     }
     // timed: a launch per chain length, as vecchia_profile_read counts them

@@ -100,6 +100,7 @@ class Batch {
     int range_off;
     int n_ranges;
     int64_t n_items;
+    int64_t most;        // items of its largest range
     int64_t sov_steps;
     std::vector<Span> spans;   // one per chain length, longest first
   };

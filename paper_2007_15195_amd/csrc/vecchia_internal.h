@@ -132,9 +132,11 @@ hipError_t launch_setup(const InstDesc* d_insts, int n_inst, const int64_t* d_te
 hipError_t launch_setup_redo(const InstDesc* d_insts, int n_inst, const int64_t* d_term_bases, int max_vars,
                              Aux64* aux64, Aux32* aux32, const int32_t* list, const int64_t* count, int64_t cap,
                              hipStream_t s);
-// A launch's items [begin, end) among those of its ranges.
+// A launch's items [begin, end) among those of its ranges. even: nearly all of them
+// in one range, so of equal work (xcd_map.h).
 struct ItemSpan {
   int64_t begin, end;
+  bool even;
 };
 // K: the most SOV steps of any term of the span. block: the launch's instances
 // are block plans (denominator split per term).

@@ -1,4 +1,4 @@
-// Reads grid sizes n from standard input and prints, for each, the slots of blocks 0..n-1 on a line.
+// Reads lines "n even" from standard input and prints, for each, the slots of blocks 0..n-1 on a line.
 #define __host__
 #define __device__
 #define __forceinline__ inline
@@ -7,9 +7,9 @@
 #include "xcd_map.h"
 
 int main() {
-  unsigned n;
-  while (std::scanf("%u", &n) == 1) {
-    for (unsigned b = 0; b < n; ++b) std::printf("%u ", vecchia::xcd_slot(b, n));
+  unsigned n, even;
+  while (std::scanf("%u %u", &n, &even) == 2) {
+    for (unsigned b = 0; b < n; ++b) std::printf("%u ", vecchia::xcd_slot(b, n, even != 0));
     std::printf("\n");
   }
   return 0;
